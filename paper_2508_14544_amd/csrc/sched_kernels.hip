@@ -1,11 +1,20 @@
-// sched_kernels.hip -- the C ABI of the scheduler simulator (host side) and
-// the kernels it launches, except the wide row ladder (sched_wide.hip) and
-// the workgroup kernels (sched_group.hip), each its own translation unit so
-// that their large bodies do not change how the other kernels are compiled.
-// The device code is in sim_device.hpp.
-#include "sim_device.hpp"
+// sched_kernels.hip -- the C ABI of the scheduler simulator (host side), the
+// preparation and launch-order kernels and, unless SK_SEPARATE_KERNELS leaves
+// them to sched_wave_*.hip (built concurrently), the one-wave kernels.  The wide
+// row ladder (sched_wide.hip) and the workgroup kernels (sched_group.hip) are
+// translation units of their own.  The device code is in sim_wave.hpp and
+// sim_device.hpp.
+#include "sim_wave.hpp"
 
 namespace sk {
+#ifdef SK_SEPARATE_KERNELS
+// defined in sched_wave_*.hip (else here)
+SK_WAVE_KERNELS(extern, SCHED_AMAX)
+SK_WAVE_KERNELS_AMIN(extern)
+SK_WAVE_KERNELS(extern, SCHED_HSF)
+SK_WAVE_KERNELS(extern, SCHED_AELL)
+SK_WAVE_KERNELS(extern, SCHED_ARANDOM)
+#endif
 // defined in sched_wide.hip
 extern template __global__ void k_simulate_ladder_wide<SCHED_AMAX>(Params);
 extern template __global__ void k_simulate_ladder_wide<SCHED_AMIN>(Params);
@@ -190,7 +199,7 @@ const void* sim_kernel(const Tier& tr, bool ordered, bool classes, bool rounds) 
   if (tr.grow)
     return tr.wide ? reinterpret_cast<const void*>(&sk::k_simulate_ladder_wide<ALGO>)
                    : reinterpret_cast<const void*>(&sk::k_simulate_ladder<ALGO>);
-  if constexpr (ALGO == SCHED_AMIN || ALGO == SCHED_AELL)
+  if constexpr (ALGO == SCHED_AMIN)
     if (tr.vglobal) return reinterpret_cast<const void*>(&sk::k_simulate<ALGO, 16, true, true>);
   if (tr.retry)
     return tr.rows <= 8    ? reinterpret_cast<const void*>(&sk::k_simulate<ALGO, 8, true>)

@@ -541,25 +541,6 @@ constexpr int kShrinkSpare = 16;
 // holds more than this many entries goes to the LDS set
 constexpr int kURowFlush = 48;
 
-// The state of an instance at step 0 (what a body starting fresh holds).
-template <typename ST>
-__device__ __forceinline__ void fresh_state(ST& st) {
-#pragma unroll
-  for (int r = 0; r < ST::kRows; ++r) {
-    st.r_end[r] = INT32_MIN; st.r_x[r] = 0; st.r_c[r] = 0x7FFFFFFF; st.r_h[r] = 0; st.r_key[r] = 0xFFFFFFFFu;
-    st.r_u[r] = 0;
-  }
-  st.fr_row = 0; st.fr_mask = ~0ull; st.N = 0; st.X = 0; st.t_r = 0; st.next_c = 0x7FFFFFFF;
-  st.aw_base = -64; st.aw_a = 0x7FFFFFFF; st.aw_rank = 0; st.arr_ptr = 0; st.next_a = 0;
-  st.f_rank = -1; st.fw_base = -1; st.f_word = 0ull; st.f_key = 0xFFFFFFFFu; st.f_so = 0; st.fw_key = 0xFFFFFFFFu;
-  st.fw_so = 0; st.f_u = 0; st.fw_u = 0; st.nV = 0; st.nVe = 0; st.v_pos = -1; st.v_head = 0;
-  st.v_key = 0xFFFFFFFFu; st.v_so = 0; st.v_u = 0; st.n_done = 0; st.retry_at = 0; st.t = 0; st.DT = 0;
-  st.rsteps = 0; st.tot_ev = 0; st.next_rows = 2; st.resume = false;
-  st.u_key = 0xFFFFFFFFu; st.u_so = 0; st.u_gate = 0; st.u_used = 0ull;
-  st.uh_key = 0xFFFFFFFFu; st.uh_so = 0; st.uh_lane = -1;
-  st.vw_lo = 0; st.vw_hi = 0; st.vw_base = -(1 << 30);
-}
-
 // ---------------------------------------------------------------------------
 // A workgroup of W > 1 waves simulating one instance.  Every wave holds its
 // own ROWS register rows of the running set (W x 64 x ROWS slots) and its own
@@ -1862,169 +1843,6 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
   return status;
 }
 
-// One wave per instance.  RETRY_PASS: only instances handed over by an
-// earlier launch for a reason this pass takes (P.run_mask) run, held to
-// P.run_cap runs at once.
-template <int ALGO, int ROWS, bool RETRY_PASS, bool VGLOBAL = false>
-__global__ __launch_bounds__(64) void k_simulate(Params P) {
-  const int k = blockIdx.x;
-  if (P.algo_of && P.algo_of[k] != ALGO) return;  // adaptive run: the other policy's instance
-  int st0 = P.status[k];
-  if (RETRY_PASS) {
-    const bool take = (st0 == kRetryRows && (P.run_mask & 1)) || (st0 == kRetryV && (P.run_mask & 2));
-    if (!take) return;
-    st0 = SCHED_OK;
-  }
-  sim_instance<ALGO, ROWS, false, false, VGLOBAL, RETRY_PASS>(P, k, st0, P.retry_status);
-}
-
-// One wave per instance on the row ladder: the simulation starts with 2
-// register rows and moves, state and all, to the body with 3, 5, 8 or 10 rows
-// as its running set grows and back down as it shrinks, so that every scan
-// covers about as many rows as the instance has runs (most of an instance's
-// events happen with at most 128 runs).  A running set beyond 640 runs ends
-// with P.retry_status.  Held to 128 VGPRs so that four waves share a SIMD.
-template <int ALGO, bool WIDE>
-__device__ __forceinline__ void ladder_instance(const Params& P, const int k) {
-  if (P.algo_of && P.algo_of[k] != ALGO) return;
-  int st0 = P.status[k];
-  if constexpr (WIDE) {
-    if (P.run_mask) {
-      // a retry pass: only the instances an earlier pass handed over
-      const bool take = (st0 == kRetryRows && (P.run_mask & 1)) || (st0 == kRetryV && (P.run_mask & 2));
-      if (!take) return;
-      st0 = SCHED_OK;
-    }
-  }
-  if (st0 == SCHED_OK) {
-    // the bodies all resume from a state, so the bitmaps and staged outputs
-    // are set up here
-    extern __shared__ uint64_t lds64[];
-    const int64_t b = P.offsets[k];
-    const int n = static_cast<int>(P.offsets[k + 1] - b);
-    const int nw = (n + 63) >> 6, nw1 = (nw + 63) >> 6;
-    for (int w = threadIdx.x; w < nw; w += 64) lds64[w] = 0;
-    for (int w = threadIdx.x; w < nw1; w += 64) lds64[P.nw_max + w] = 0;
-    int32_t* lc = reinterpret_cast<int32_t*>(lds64 + P.nw_max + P.nw1_max + P.cap_v);
-    if (P.stage_comp)
-      for (int i = threadIdx.x; i < n; i += 64) lc[i] = -1;
-    __syncthreads();
-  }
-  const bool empty = st0 == SCHED_OK && P.offsets[k + 1] == P.offsets[k];
-  if (st0 != SCHED_OK || empty) {
-    // nothing to simulate: zero totals (the per-request outputs were set by
-    // the preparation)
-    if (threadIdx.x == 0) {
-      P.total_latency[k] = 0;
-      if (P.makespan) P.makespan[k] = 0;
-      if (P.request_steps) P.request_steps[k] = 0;
-      if (P.total_evictions) P.total_evictions[k] = 0;
-      P.status[k] = st0;
-    }
-    return;
-  }
-  using ST = typename std::conditional<WIDE, SimStateWide, SimState>::type;
-  ST st;
-  fresh_state(st);
-  int r;
-  if constexpr (!WIDE) {
-    do {
-      switch (st.next_rows) {
-        case 2: r = sim_instance<ALGO, 2, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 3: r = sim_instance<ALGO, 3, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 5: r = sim_instance<ALGO, 5, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 8: r = sim_instance<ALGO, 8, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        default: r = sim_instance<ALGO, 10, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-      }
-    } while (r == kResume);
-  } else {
-    do {
-      switch (st.next_rows) {
-        case 2: r = sim_instance<ALGO, 2, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 3: r = sim_instance<ALGO, 3, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 5: r = sim_instance<ALGO, 5, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 8: r = sim_instance<ALGO, 8, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 10: r = sim_instance<ALGO, 10, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 12: r = sim_instance<ALGO, 12, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        default: r = sim_instance<ALGO, 16, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-      }
-    } while (r == kResume);
-  }
-}
-
-// The narrow ladder: one wave per instance moving along the bodies of 2 to
-// 10 rows (the body of the two kernels below; ORDERED_: workgroup g simulates
-// instance P.order[g]; CLS_: issue priorities by P.pclass; PRIO_ false: the
-// waves keep the default issue priority, for batches in which priorities
-// cannot help (a wave per SIMD, or rounds of waves) but would cost scalar
-// instructions).
-#define SK_NARROW_LADDER(ORDERED_, CLS_, PRIO_)                                                                                               \
-  const int k = (ORDERED_) ? P.order[blockIdx.x] : static_cast<int>(blockIdx.x);                                                       \
-  if (P.algo_of && P.algo_of[k] != ALGO) return;                                                                                       \
-  const int st0 = P.status[k];                                                                                                         \
-  if (st0 == SCHED_OK) {                                                                                                               \
-    /* the bodies all resume from a state, so the bitmaps and staged outputs */                                                        \
-    /* are set up here */                                                                                                              \
-    extern __shared__ uint64_t lds64[];                                                                                                \
-    const int64_t b = P.offsets[k];                                                                                                    \
-    const int n = static_cast<int>(P.offsets[k + 1] - b);                                                                              \
-    const int nw = (n + 63) >> 6, nw1 = (nw + 63) >> 6;                                                                                \
-    for (int w = threadIdx.x; w < nw; w += 64) lds64[w] = 0;                                                                           \
-    for (int w = threadIdx.x; w < nw1; w += 64) lds64[P.nw_max + w] = 0;                                                               \
-    int32_t* lc = reinterpret_cast<int32_t*>(lds64 + P.nw_max + P.nw1_max + P.cap_v);                                                  \
-    if (P.stage_comp)                                                                                                                  \
-      for (int i = threadIdx.x; i < n; i += 64) lc[i] = -1;                                                                            \
-    __syncthreads();                                                                                                                   \
-  }                                                                                                                                    \
-  const bool empty = st0 == SCHED_OK && P.offsets[k + 1] == P.offsets[k];                                                              \
-  if (st0 != SCHED_OK || empty) {                                                                                                      \
-    /* nothing to simulate: zero totals (the per-request outputs were set by */                                                        \
-    /* the preparation) */                                                                                                             \
-    if (threadIdx.x == 0) {                                                                                                            \
-      P.total_latency[k] = 0;                                                                                                          \
-      if (P.makespan) P.makespan[k] = 0;                                                                                               \
-      if (P.request_steps) P.request_steps[k] = 0;                                                                                     \
-      if (P.total_evictions) P.total_evictions[k] = 0;                                                                                 \
-      P.status[k] = st0;                                                                                                               \
-    }                                                                                                                                  \
-    return;                                                                                                                            \
-  }                                                                                                                                    \
-  SimState st;                                                                                                                         \
-  fresh_state(st);                                                                                                                     \
-  int r;                                                                                                                               \
-  do {                                                                                                                                 \
-    switch (st.next_rows) {                                                                                                            \
-      case 2: r = sim_instance<ALGO, 2, true, true, false, false, SimState, 1, (CLS_), (PRIO_)>(P, k, SCHED_OK, P.retry_status, &st); break;    \
-      case 3: r = sim_instance<ALGO, 3, true, true, false, false, SimState, 1, (CLS_), (PRIO_)>(P, k, SCHED_OK, P.retry_status, &st); break;    \
-      case 5: r = sim_instance<ALGO, 5, true, true, false, false, SimState, 1, (CLS_), (PRIO_)>(P, k, SCHED_OK, P.retry_status, &st); break;    \
-      case 8: r = sim_instance<ALGO, 8, true, true, false, false, SimState, 1, (CLS_), (PRIO_)>(P, k, SCHED_OK, P.retry_status, &st); break;    \
-      default: r = sim_instance<ALGO, 10, true, true, false, false, SimState, 1, (CLS_), (PRIO_)>(P, k, SCHED_OK, P.retry_status, &st); break;  \
-    }                                                                                                                                  \
-  } while (r == kResume);
-
-// The narrow ladder held to 128 VGPRs so that four waves share a SIMD; each
-// (ORDERED, CLS, PRIO) choice is an instance of the kernel of its own, so
-// that the other launches compile without it.
-template <int ALGO, bool ORDERED = false, bool CLS = false, bool PRIO = true>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_simulate_ladder(Params P) {
-  SK_NARROW_LADDER(ORDERED, CLS, PRIO);
-}
-
-// The same bodies with 256 VGPRs (fewer spills), for batches in which every
-// wave has a SIMD to itself (so without issue priorities).
-template <int ALGO>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_simulate_ladder_roomy(Params P) {
-  SK_NARROW_LADDER(false, false, false);
-}
-#undef SK_NARROW_LADDER
-
-// The wide ladder (up to 1024 runs): for batches of few instances, where
-// registers matter more than occupancy, and for the instances that outgrow
-// the narrow ladder (a retry pass).
-template <int ALGO>
-__global__ __launch_bounds__(64) void k_simulate_ladder_wide(Params P) {
-  ladder_instance<ALGO, true>(P, blockIdx.x);
-}
 // A workgroup of W waves per instance, ROWS register rows each (W x 64 x ROWS
 // runs): for few large instances, and for the instances whose running set
 // outgrows one wave's rows (a retry pass).  With P.run_mask set, only the

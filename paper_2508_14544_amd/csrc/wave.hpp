@@ -16,6 +16,8 @@ constexpr int kDppQuadXor1 = 0xB1;    // quad_perm [1,0,3,2]
 constexpr int kDppQuadXor2 = 0x4E;    // quad_perm [2,3,0,1]
 constexpr int kDppRowHalfMirror = 0x141;
 constexpr int kDppRowMirror = 0x140;
+constexpr int kDppWaveShl1 = 0x130;  // lane i reads lane i + 1
+constexpr int kDppWaveShr1 = 0x138;  // lane i reads lane i - 1
 
 __device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 
@@ -115,6 +117,18 @@ __device__ __forceinline__ int32_t sum_i32_all(int32_t v) {
   return static_cast<int32_t>(fold_in_row(fold_rows(static_cast<uint32_t>(v), OpAddU32{}), OpAddU32{}));
 }
 
+// Four sums at once: lanes 16 q to 16 q + 15 get the sum of vq over the wave.
+// The lane swaps put two half-folded values into one register, so the four
+// share one in-row fold: 10 instructions where four sums of their own take 32.
+__device__ __forceinline__ int32_t sum4_i32(int32_t v0, int32_t v1, int32_t v2, int32_t v3) {
+  const auto a = __builtin_amdgcn_permlane32_swap(static_cast<uint32_t>(v0), static_cast<uint32_t>(v2), false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(static_cast<uint32_t>(v1), static_cast<uint32_t>(v3), false, false);
+  const uint32_t s02 = static_cast<uint32_t>(a[0]) + static_cast<uint32_t>(a[1]);
+  const uint32_t s13 = static_cast<uint32_t>(b[0]) + static_cast<uint32_t>(b[1]);
+  const auto q = __builtin_amdgcn_permlane16_swap(s02, s13, false, false);
+  return static_cast<int32_t>(fold_in_row(static_cast<uint32_t>(q[0]) + static_cast<uint32_t>(q[1]), OpAddU32{}));
+}
+
 // The minimum left in every lane, for locating it with a ballot without a
 // round trip through a scalar register.
 __device__ __forceinline__ uint32_t min_u32_all(uint32_t v) { return fold_in_row(fold_rows(v, OpMinU32{}), OpMinU32{}); }
@@ -123,6 +137,80 @@ __device__ __forceinline__ uint32_t min_u32(uint32_t v) {
   const uint32_t r = fold_in_row(fold_rows(v, OpMinU32{}), OpMinU32{});
   return static_cast<uint32_t>(uniform(static_cast<int32_t>(r)));
 }
+
+// Stores and atomics of the lanes in `mask`, for code that a whole wave runs
+// with every lane active (exec is all ones before and after).  A branch on the
+// lane would do the same, but one such branch inside a loop makes the compiler
+// rebuild the loop's whole control flow out of condition masks (it only leaves
+// regions alone whose branches are all uniform); with these, a loop whose
+// other branches are uniform keeps plain scalar branches.  The compiler does not
+// count these operations: its own waits for later loads still hold (the counters
+// are in order, so an extra operation only makes them stricter), and code that
+// reads the stored values from global memory waits with wait_stores first (LDS
+// operations of a wave are executed in order).
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+  return static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void*)(p)));
+}
+#ifdef __OPTIMIZE__
+__device__ __forceinline__ void lds_store32(uint64_t mask, uint32_t at, uint32_t v) {
+  asm volatile("s_mov_b64 exec, %0\n\tds_write_b32 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(mask), "v"(at), "v"(v) : "memory");
+}
+__device__ __forceinline__ void lds_store64(uint64_t mask, uint32_t at, uint64_t v) {
+  asm volatile("s_mov_b64 exec, %0\n\tds_write_b64 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(mask), "v"(at), "v"(v) : "memory");
+}
+__device__ __forceinline__ void lds_or64(uint64_t mask, uint32_t at, uint64_t v) {
+  asm volatile("s_mov_b64 exec, %0\n\tds_or_b64 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(mask), "v"(at), "v"(v) : "memory");
+}
+__device__ __forceinline__ void lds_and64(uint64_t mask, uint32_t at, uint64_t v) {
+  asm volatile("s_mov_b64 exec, %0\n\tds_and_b64 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(mask), "v"(at), "v"(v) : "memory");
+}
+__device__ __forceinline__ void global_store32(uint64_t mask, const void* at, uint32_t v) {
+  asm volatile("s_mov_b64 exec, %0\n\tglobal_store_dword %1, %2, off\n\ts_mov_b64 exec, -1" ::"s"(mask), "v"(at), "v"(v)
+               : "memory");
+}
+__device__ __forceinline__ void global_store64(uint64_t mask, const void* at, uint64_t v) {
+  asm volatile("s_mov_b64 exec, %0\n\tglobal_store_dwordx2 %1, %2, off\n\ts_mov_b64 exec, -1" ::"s"(mask), "v"(at), "v"(v)
+               : "memory");
+}
+// (device scope: the counts are in the L2 that every CU of the XCD shares, as a
+// plain agent-scope fetch-add without a result)
+__device__ __forceinline__ void global_add32(uint64_t mask, const void* at, uint32_t v) {
+  asm volatile("s_mov_b64 exec, %0\n\tglobal_atomic_add %1, %2, off\n\ts_mov_b64 exec, -1" ::"s"(mask), "v"(at), "v"(v)
+               : "memory");
+}
+#else
+// (without optimisation a uniform value need not be in a scalar register: there
+// the branch on the lane it is)
+__device__ __forceinline__ bool in_mask(uint64_t mask) { return (mask >> lane_id()) & 1ull; }
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(3))) T* lds_at(uint32_t at) {
+  return (__attribute__((address_space(3))) T*)(static_cast<uintptr_t>(at));
+}
+__device__ __forceinline__ void lds_store32(uint64_t mask, uint32_t at, uint32_t v) {
+  if (in_mask(mask)) *lds_at<uint32_t>(at) = v;
+}
+__device__ __forceinline__ void lds_store64(uint64_t mask, uint32_t at, uint64_t v) {
+  if (in_mask(mask)) *lds_at<uint64_t>(at) = v;
+}
+__device__ __forceinline__ void lds_or64(uint64_t mask, uint32_t at, uint64_t v) {
+  if (in_mask(mask)) __hip_atomic_fetch_or(lds_at<uint64_t>(at), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_and64(uint64_t mask, uint32_t at, uint64_t v) {
+  if (in_mask(mask)) __hip_atomic_fetch_and(lds_at<uint64_t>(at), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void global_store32(uint64_t mask, const void* at, uint32_t v) {
+  if (in_mask(mask)) *static_cast<uint32_t*>(const_cast<void*>(at)) = v;
+}
+__device__ __forceinline__ void global_store64(uint64_t mask, const void* at, uint64_t v) {
+  if (in_mask(mask)) *static_cast<uint64_t*>(const_cast<void*>(at)) = v;
+}
+__device__ __forceinline__ void global_add32(uint64_t mask, const void* at, uint32_t v) {
+  if (in_mask(mask))
+    __hip_atomic_fetch_add(static_cast<uint32_t*>(const_cast<void*>(at)), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+#endif
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // 64-bit sums for the epilogue (not on the hot path).
 __device__ __forceinline__ int64_t sum_i64(int64_t v) {
