@@ -45,6 +45,12 @@
 
 namespace sk {
 
+// A branch that the step loop rarely takes: the code behind it is placed out of
+// the way, since a lone wave waits about 30 cycles for its instructions after
+// every jump taken.
+#define SK_RARE(COND) __builtin_expect(!!(COND), 0)
+#define SK_USUAL(COND) __builtin_expect(!!(COND), 1)
+
 // The loop-carried state of one instance, handed from one body to another with
 // a different number of register rows (the row ladder: 2, 3, 5, 8, 10, then 12
 // and 16 rows).  A body grows at an admission that finds no free slot (the next
@@ -282,11 +288,12 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
   for (int q_ = 0; q_ < (NP_); ++q_) {                                               \
     const uint32_t ik_ = wave::readlane_u(pn_key, q_), is_ = wave::readlane_u(pn_so, q_); \
     int p_ = __builtin_popcountll(wave::ballot(vw_key < ik_));                       \
-    if (v_lo == 0) {                                                                 \
+    if (SK_RARE(v_lo == 0)) {                                                        \
       if (v_hi > 32) {                                                               \
         if (v_sp + v_hi - 24 > cap_v - n_ovf) {                                      \
           status = P.retry_v_status;                                                 \
-          break;                                                                     \
+          q_ = (NP_);                                                                \
+          continue;                                                                  \
         }                                                                            \
         v_store(lane_span(24, v_hi), v_sp + v_hi - 1 - lane, (static_cast<uint64_t>(vw_so) << 32) | vw_key); \
         v_sp += v_hi - 24;                                                           \
@@ -300,10 +307,11 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
       v_hi += 32;                                                                    \
       p_ = __builtin_popcountll(wave::ballot(vw_key < ik_));                         \
     }                                                                                \
-    if (p_ == v_hi && v_sp > 0) {                                                    \
+    if (SK_RARE(p_ == v_hi && v_sp > 0)) {                                           \
       if (v_sp + 1 > cap_v - n_ovf) {                                                \
         status = P.retry_v_status;                                                   \
-        break;                                                                       \
+        q_ = (NP_);                                                                  \
+        continue;                                                                    \
       }                                                                              \
       int moved_ = 0;                                                                \
       for (;;) {                                                                     \
@@ -374,7 +382,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
     int32_t prio_next = 0;
 #define SK_SET_PRIORITY()                                                            \
   do {                                                                               \
-    if (PRIO && n_done >= prio_next) {                                               \
+    if (PRIO && SK_RARE(n_done >= prio_next)) {                                      \
       const int left_ = n - n_done;                                                  \
       int lv_;                                                                       \
       if (pcls >= 0) {                                                               \
@@ -439,11 +447,11 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
     for (;;) {
       if (mode != kNext) {
       if (mode == kStep) {
-      if (t > cap) {
+      if (SK_RARE(t > cap)) {
         status = SCHED_E_STEP_CAP;
         goto ended;
       }
-      if (t - t_r >= kRebase) {
+      if (SK_RARE(t - t_r >= kRebase)) {
         const int32_t d = t - t_r;
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) r_x[r] = static_cast<int32_t>(static_cast<uint32_t>(r_x[r]) + static_cast<uint32_t>(d));
@@ -451,7 +459,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
         t_r = t;
       }
       // ---- 1. arrivals; requests cancelled at the previous step become eligible
-      if (t >= next_a) {
+      if (SK_RARE(t >= next_a)) {
         const int32_t head = f_word != 0ull ? f_base + __builtin_ctzll(f_word) : -1;
         // the cached word goes back to LDS before arrivals set bits in it
         if (f_word != 0ull) wave::lds_store64(1ull, l0_at + 8u * static_cast<uint32_t>(f_base >> 6), f_word);
@@ -468,30 +476,31 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
           if (arr_ptr >= aw_base + 64) SK_LOAD_ARRIVALS();
           next_a = wave::readlane(aw_a, arr_ptr - aw_base);
         } else {
-          next_a = kNever;
+          next_a = wave::in_sgpr(kNever);
         }
         SK_F_FIND();
-        if (head != f_base + __builtin_ctzll(f_word | (1ull << 63))) retry_at = 0;
+        if (head != f_base + __builtin_ctzll(f_word | (1ull << 63))) retry_at = wave::in_sgpr(0);
       }
       if (kAmin && n_pend > 0) {
         SK_V_INSERT(n_pend);
-        while (n_ovf > 0 && status == SCHED_OK) {
-          // 64 more from the last slots of the stack's array
-          const uint64_t e = v_load(cap_v - n_ovf + lane);
+        while (SK_RARE(n_ovf > 0 && status == SCHED_OK)) {
+          // up to 64 more from the last slots of the stack's array
+          const int c = n_ovf < 64 ? n_ovf : 64;
+          const uint64_t e = v_load(cap_v - n_ovf + (lane < c ? lane : 0));
           pn_key = static_cast<uint32_t>(e);
           pn_so = static_cast<uint32_t>(e >> 32);
-          n_ovf -= 64;
-          SK_V_INSERT(64);
+          n_ovf -= c;
+          SK_V_INSERT(c);
         }
-        if (status != SCHED_OK) goto ended;
+        if (SK_RARE(status != SCHED_OK)) goto ended;
         n_pend = 0;
-        retry_at = 0;
+        retry_at = wave::in_sgpr(0);
       }
 
       // ---- 2. completions up to t (the policies whose runs all end as planned
       // may have passed several steps with completions, see the jump below); DT =
       // memory the runs that complete at t still hold (s + o each)
-      DT = 0;
+      DT = wave::in_sgpr(0);
       {
       bool stale_c = false;           // next_c has to be found again
       if (t >= next_c) {
@@ -514,7 +523,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
                 const int32_t ek = wave::readlane(r_end[r], ln);
                 if (ek > t + 1) {
                   SK_DROP_SHARE(wave::readlane(r_x[r], ln), ek);
-                  retry_at = 0;
+                  retry_at = wave::in_sgpr(0);
                 }
               }
             }
@@ -532,7 +541,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
             if (r == fr_row) fr_mask |= m;
           }
         }
-        if (ndone) {
+        if (SK_USUAL(ndone > 0)) {
           // (the sums are that run's values in its lane when one run completes)
           int32_t sxw;
           if (kOnPlan) {
@@ -559,7 +568,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
           SK_SET_PRIORITY();
         }
         // ---- 3. done?
-        if (n_done == n) goto ended;
+        if (SK_RARE(n_done == n)) goto ended;
         // ---- 3'. A_l: a run still present at its planned end t (planned with
         // l, so o > l) is promoted: it leaves, plans with u and joins the back of
         // the queue, lowest index first among this step's promotions
@@ -614,61 +623,84 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
       if (kAmin) {
         Pm = X + N * (t + 1 - t_r);
         if (Pm > M) {
+          // which: the runs with the smallest keys until the rest fits (k_next:
+          // one above the last key taken; the others' keys less k_next, the taken
+          // ones' wrapping round to the top)
+          uint32_t k_next = 0u;
           do {
-            uint32_t best = r_key[0];
+            uint32_t best = r_key[0] - k_next;
 #pragma unroll
-            for (int r = 1; r < ROWS; ++r) best = r_key[r] < best ? r_key[r] : best;
-            const uint32_t kmin = wave::min_u32(best);
-            if (n_pend == 64) {
-              // the pending row goes to the last free slots of the stack's array
-              if (v_sp + n_ovf + 64 > cap_v) {
-                status = P.retry_v_status;
-                break;
-              }
-              n_ovf += 64;
-              v_store(~0ull, cap_v - n_ovf + lane, (static_cast<uint64_t>(pn_so) << 32) | pn_key);
-              if (P.evictions) wave::global_add32(~0ull, ev_at + (pn_key & kIdxMask), 1u);
-              n_pend = 0;
+            for (int r = 1; r < ROWS; ++r) {
+              const uint32_t kk = r_key[r] - k_next;
+              best = kk < best ? kk : best;
             }
-            // keys differ, so one slot matches: its fields, and the slot emptied
+            const uint32_t kmin = wave::min_u32(best) + k_next;
+            // keys differ, so one slot matches
             uint64_t at = 0ull;
-            int32_t es = 0, xs = 0, cs = 0;
+            int32_t xs = 0;
 #pragma unroll
             for (int r = 0; r < ROWS; ++r) {
               const bool hit = r_key[r] == kmin;
-              const uint64_t m = wave::ballot(hit);
-              at |= m;
-              es = hit ? r_end[r] : es;
+              at |= wave::ballot(hit);
               xs = hit ? r_x[r] : xs;
-              cs = hit ? r_c[r] : cs;
-              r_end[r] = hit ? kEmpty : r_end[r];
-              r_c[r] = hit ? kNever : r_c[r];
-              r_key[r] = hit ? 0xFFFFFFFFu : r_key[r];
-              fr_mask |= r == fr_row ? m : 0ull;
             }
-            const int ln = __builtin_ctzll(at);
-            const int32_t ek = wave::readlane(es, ln), xk = wave::readlane(xs, ln), ck = wave::readlane(cs, ln);
-            if (ek > t + 1) SK_DROP_SHARE(xk, ek);
+            const int32_t xk = wave::readlane(xs, __builtin_ctzll(at));
             X -= xk;
             N -= 1;
             Pm -= xk + t + 1 - t_r;
-            stale_c = stale_c || ck == next_c;
-            const int32_t oh = static_cast<int32_t>(kmin >> kIdxBits);
-            const int32_t pk = ek - oh;
-            const int32_t gen = t - pk;
-            const int32_t nh = gen > oh ? gen : oh;
-            const uint32_t so = static_cast<uint32_t>(xk - t_r + pk) | (static_cast<uint32_t>(ck - pk) << 16);
-            // pending, startable from the next step
-            pn_key = wave::writelane_u(pn_key, (static_cast<uint32_t>(nh) << kIdxBits) | (kmin & kIdxMask), n_pend);
-            pn_so = wave::writelane_u(pn_so, so, n_pend);
-            ++n_pend;
+            k_next = kmin + 1u;
             // (no run left means no memory held)
           } while (Pm > M && N > 0);
-          if (status != SCHED_OK) goto ended;
+          // then all of them at once: out of their slots, with what they would
+          // plan with, into the pending row, startable from the next step
+#pragma unroll
+          for (int r = 0; r < ROWS; ++r) {
+            uint64_t cm = wave::ballot(r_key[r] < k_next);
+            if (cm == 0ull) continue;
+            const int c = __builtin_popcountll(cm);
+            if (SK_RARE(n_pend + c > 64)) {
+              // the pending row first goes to the last free slots of the stack's array
+              if (v_sp + n_ovf + n_pend > cap_v) {
+                status = P.retry_v_status;
+                break;
+              }
+              n_ovf += n_pend;
+              v_store(lane_span(0, n_pend), cap_v - n_ovf + lane, (static_cast<uint64_t>(pn_so) << 32) | pn_key);
+              if (P.evictions) wave::global_add32(lane_span(0, n_pend), ev_at + (pn_key & kIdxMask), 1u);
+              tot_ev += n_pend;
+              n_pend = 0;
+            }
+            const bool gone = r_key[r] < k_next;
+            const int32_t oh = static_cast<int32_t>(r_key[r] >> kIdxBits);
+            const int32_t pk = r_end[r] - oh;
+            const int32_t gen = t - pk;
+            const int32_t nh = gen > oh ? gen : oh;
+            const uint32_t nkey = (static_cast<uint32_t>(nh) << kIdxBits) | (r_key[r] & kIdxMask);
+            const uint32_t so = static_cast<uint32_t>(r_x[r] - t_r + pk) | (static_cast<uint32_t>(r_c[r] - pk) << 16);
+            stale_c = stale_c || (wave::ballot(r_c[r] == next_c) & cm) != 0ull;
+            uint64_t fm = wave::ballot(r_end[r] > t + 1) & cm;   // those with shares ahead
+            if (r == fr_row) fr_mask |= cm;
+            do {
+              const int ln = __builtin_ctzll(cm);
+              cm &= cm - 1ull;
+              pn_key = wave::writelane_u(pn_key, wave::readlane_u(nkey, ln), n_pend);
+              pn_so = wave::writelane_u(pn_so, wave::readlane_u(so, ln), n_pend);
+              ++n_pend;
+            } while (cm != 0ull);
+            while (fm != 0ull) {
+              const int ln = __builtin_ctzll(fm);
+              fm &= fm - 1ull;
+              SK_DROP_SHARE(wave::readlane(r_x[r], ln), wave::readlane(r_end[r], ln));
+            }
+            r_end[r] = gone ? kEmpty : r_end[r];
+            r_c[r] = gone ? kNever : r_c[r];
+            r_key[r] = gone ? 0xFFFFFFFFu : r_key[r];
+          }
+          if (SK_RARE(status != SCHED_OK)) goto ended;
           // the cancellation counts of the step's pending requests at once
           if (P.evictions) wave::global_add32(lane_span(0, n_pend), ev_at + (pn_key & kIdxMask), 1u);
-          tot_ev += n_pend + n_ovf;
-          retry_at = 0;
+          tot_ev += n_pend;
+          retry_at = wave::in_sgpr(0);
         }
       }
       if (stale_c) {
@@ -699,7 +731,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
         else if (ROWS > 8 && N <= 64 * 8 - kShrinkSpare) target = 8;
         else if (ROWS > 10 && N <= 64 * 10 - kShrinkSpare) target = 10;
         else if (ROWS > 12 && N <= 64 * 12 - kShrinkSpare) target = 12;
-        if (target > 0) {
+        if (SK_RARE(target > 0)) {
           uint64_t fm[ROWS];
 #pragma unroll
           for (int r = 0; r < ROWS; ++r) fm[r] = wave::ballot(r_end[r] == kEmpty);
@@ -745,7 +777,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
       // ---- 5. admission of the longest feasible prefix in key order, one
       // candidate an iteration.  wait_until: the step before which the head
       // cannot start unless something else happens (kNever: it waits for that).
-      wait_until = kNever;
+      wait_until = wave::in_sgpr(kNever);
       if (t < retry_at) {
         wait_until = retry_at;
         goto admitted;
@@ -758,7 +790,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
         // with no candidate of the other set between them (A_l: every fresh
         // request comes before the promoted ones)
         q_at = 64;
-        if (f_word == 0ull && f_base >= 0) {
+        if (SK_RARE(f_word == 0ull && f_base >= 0)) {
           // the word in scalar registers has been emptied: the next one
           const int j0 = f_base >> 6;
           wave::lds_store64(1ull, l0_at + 8u * static_cast<uint32_t>(j0), 0ull);
@@ -768,7 +800,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
         }
         rest = f_word;
         if constexpr (kAmin) {
-          if (v_lo == v_hi && v_sp > 0) {
+          if (SK_RARE(v_lo == v_hi && v_sp > 0)) {
             // refill the register row from the top of the stack
             const int c = v_sp < 32 ? v_sp : 32;
             const int j = v_sp + 15 - lane;  // lane 16 gets the top
@@ -796,7 +828,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
         }
         if (rest == 0ull) {
           // nothing waits
-          if (kDrains && next_a == kNever) {
+          if (kDrains && SK_RARE(next_a == kNever)) {
             // nor will anything: the runs end as they are.  A run that completes at
             // C <= cap counts at steps t to C - 1, another to the cap
             int32_t left = 0;
@@ -813,7 +845,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
             if (wave::ballot(left != 0) != 0ull) status = SCHED_E_STEP_CAP;
             goto ended;
           }
-          wait_until = kOnPlan ? next_a : kNever;
+          wait_until = kOnPlan ? next_a : wave::in_sgpr(kNever);
           goto admitted;
         }
       }
@@ -823,13 +855,11 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
         const int j = __builtin_ctzll(rest);
         const uint32_t c_so = wave::readlane_u(bso, j);
         const int32_t s = static_cast<int32_t>(c_so & 0xFFFFu);
-        if (Pm + s + 1 > M) {
-          wait_until = kNever;
-          goto admitted;
-        }
-        // step t (runs completing at t hold s+o); implied by step t+1 when DT = 0
-        if (DT > 0 && DT + Pm - N + s > M) {
-          wait_until = t + 1;
+        // step t + 1, and step t, at which runs completing at t hold s + o (the
+        // latter is implied by the former when DT = 0)
+        const int32_t at_t = Pm + (DT - N);
+        if ((Pm + 1 > at_t ? Pm + 1 : at_t) + s > M) {
+          wait_until = Pm + s + 1 > M ? wave::in_sgpr(kNever) : t + 1;
           goto admitted;
         }
         const uint32_t c_key = wave::readlane_u(bkey, j);
@@ -892,7 +922,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
           q_at = 0;
         }
         const int32_t fe = wave::readlane(gf, q_at) + s + est;
-        if (est > 1 && fe > M) {
+        if (SK_RARE(est > 1 && fe > M)) {
           // f at the sliding end only grows until it passes the next planned end
           int32_t emin = kNever;
 #pragma unroll
@@ -906,11 +936,11 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
         }
         // admit: start at p = t, in a free slot (without one nothing has
         // changed for this candidate)
-        if (CAPPED && N >= P.run_cap) {
+        if (CAPPED && SK_RARE(N >= P.run_cap)) {
           status = retry_status;
           goto ended;
         }
-        if (fr_mask == 0ull) {
+        if (SK_RARE(fr_mask == 0ull)) {
           int rr = -1;
           uint64_t mm = 0ull;
 #pragma unroll
@@ -919,7 +949,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
             rr = m ? r : rr;
             mm = m ? m : mm;
           }
-          if (rr < 0) {
+          if (SK_RARE(rr < 0)) {
             // hand the state at this admission to the body above, if there is one
             handoff = TO_STATE ? ladder_up(ROWS, kStateRows) : 0;
             status = handoff > 0 ? kResume : retry_status;
@@ -959,7 +989,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
         } else {
           f_word &= f_word - 1ull;
         }
-        retry_at = 0;
+        retry_at = wave::in_sgpr(0);
         mode = kNext;
         continue;
       }
@@ -978,9 +1008,9 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
         // processed.
         int32_t jump = wait_until;
         if (!(kOnPlan && wait_until <= cap)) jump = next_c < jump ? next_c : jump;
-        jump = next_a < jump ? next_a : jump;
+        jump = wave::in_sgpr(next_a < jump ? next_a : jump);
         const int32_t lim = t_r + kRebase;
-        jump = lim < jump ? lim : jump;
+        jump = wave::in_sgpr(lim < jump ? lim : jump);
         jump = cap + 1 < jump ? cap + 1 : jump;
         if (kAmin && N > 0) {
           // first step whose projection exceeds M, if it comes before the jump
@@ -1082,6 +1112,8 @@ __device__ __forceinline__ void finish_instance(const Params& P, const int k, co
   }
 }
 #undef SK_SET_PRIORITY
+#undef SK_RARE
+#undef SK_USUAL
 #undef SK_SAVE_STATE
 #undef SK_LOAD_ARRIVALS
 #undef SK_F_FIND

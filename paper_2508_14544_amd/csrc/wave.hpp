@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace wave {
 
 constexpr int kDppQuadXor1 = 0xB1;    // quad_perm [1,0,3,2]
@@ -64,9 +66,23 @@ __device__ __forceinline__ T in_vgpr(T v) {
   return v;
 }
 
+// The same value, opaque to the compiler and in a scalar register: for a uniform
+// value that would otherwise be drawn into vector code (a constant that a vector
+// instruction of the same block uses too, a chain of minima that becomes one
+// three-operand vector minimum), which would take every branch on it along.
+__device__ __forceinline__ int32_t in_sgpr(int32_t v) {
+  v = __builtin_amdgcn_readfirstlane(v);  // (no instruction where it is in one already)
+#ifdef __OPTIMIZE__
+  asm("" : "+s"(v));
+#endif
+  return v;
+}
+
+// (every control used reads some lane for every lane, or leaves the rest to
+// the caller, so the old value does not matter)
 template <int CTRL>
 __device__ __forceinline__ int32_t dpp(int32_t v) {
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);
 }
 
 // Cross-row folds (gfx950): after fold_rows every lane holds OP over the four
@@ -101,14 +117,32 @@ struct OpMinU32 {
   __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a < b ? a : b; }
 };
 
+// The fold left in lane 63 only: inside each row by row_shr 1, 2, 4, 8, then
+// from row to row by row_bcast 15 and 31, one instruction a step (a lane without
+// a source folds `none`, the identity, which the hardware does by not writing
+// it).  12 instructions with their wait states, where folding the rows with lane
+// swaps first takes 17: for results that go to a scalar register at once.
+template <uint32_t NONE, typename F>
+__device__ __forceinline__ uint32_t fold_to_last(uint32_t v, F op) {
+  auto step = [&](auto ctrl, auto rows) {
+    v = op(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int32_t>(NONE), static_cast<int32_t>(v),
+                                                                decltype(ctrl)::value, decltype(rows)::value, 0xF, false)));
+  };
+  step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});
+  step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});
+  step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});
+  step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});
+  step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});
+  step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});
+  return v;
+}
+
 __device__ __forceinline__ int32_t max_i32(int32_t v) {
-  const uint32_t r = fold_in_row(fold_rows(static_cast<uint32_t>(v), OpMaxI32{}), OpMaxI32{});
-  return uniform(static_cast<int32_t>(r));
+  return readlane(static_cast<int32_t>(fold_to_last<0x80000000u>(static_cast<uint32_t>(v), OpMaxI32{})), 63);
 }
 
 __device__ __forceinline__ int32_t sum_i32(int32_t v) {
-  const uint32_t r = fold_in_row(fold_rows(static_cast<uint32_t>(v), OpAddU32{}), OpAddU32{});
-  return uniform(static_cast<int32_t>(r));
+  return readlane(static_cast<int32_t>(fold_to_last<0u>(static_cast<uint32_t>(v), OpAddU32{})), 63);
 }
 
 // The sum left in every lane (a vector value): for tests that combine it with
@@ -134,8 +168,7 @@ __device__ __forceinline__ int32_t sum4_i32(int32_t v0, int32_t v1, int32_t v2, 
 __device__ __forceinline__ uint32_t min_u32_all(uint32_t v) { return fold_in_row(fold_rows(v, OpMinU32{}), OpMinU32{}); }
 
 __device__ __forceinline__ uint32_t min_u32(uint32_t v) {
-  const uint32_t r = fold_in_row(fold_rows(v, OpMinU32{}), OpMinU32{});
-  return static_cast<uint32_t>(uniform(static_cast<int32_t>(r)));
+  return readlane_u(fold_to_last<0xFFFFFFFFu>(v, OpMinU32{}), 63);
 }
 
 // Stores and atomics of the lanes in `mask`, for code that a whole wave runs
