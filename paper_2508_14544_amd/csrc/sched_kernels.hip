@@ -4,6 +4,7 @@
 // row ladder (sched_wide.hip) and the workgroup kernels (sched_group.hip) are
 // translation units of their own.  The device code is in sim_wave.hpp and
 // sim_device.hpp.
+#include "sim_tiny.hpp"
 #include "sim_wave.hpp"
 
 namespace sk {
@@ -398,6 +399,41 @@ sk::Params base_params(const sched_instances_t* in, int64_t M) {
   return P;
 }
 
+sk::Params result_params(const sched_instances_t* in, int64_t M, const sched_results_t* out, int64_t step_cap) {
+  sk::Params P = base_params(in, M);
+  P.completion = out->completion;
+  P.evictions = out->evictions;
+  P.total_latency = out->total_latency;
+  P.makespan = out->makespan;
+  P.request_steps = out->request_steps;
+  P.total_evictions = out->total_evictions;
+  P.status = out->status;
+  P.algo_used = out->algo_used;
+  P.step_cap = step_cap;
+  return P;
+}
+
+// Whether a batch of K instances of at most nmax requests runs a lane per
+// instance (k_tiny).  Instances of up to two requests always (12 us a call
+// against 26 to 40 with a wave each, A_min, at any K up to 4096); of up to eight
+// once a wave each would take more than five rounds of the 16 waves per CU (A_min,
+// 6 requests, lane against wave: 118 and 100 us at 16384 instances, 124 and 297 us
+// at 65536; 8 requests: 163 and 115, 179 and 360 us).
+bool tiny_batch(int64_t nmax, int64_t K, int n_cu) {
+  return nmax <= 2 || (nmax <= sk::kTinyRequests && K > 5 * 16 * static_cast<int64_t>(n_cu));
+}
+
+const void* tiny_kernel(int algo) {
+  switch (algo) {
+    case SCHED_AMAX: return reinterpret_cast<const void*>(&sk::k_tiny<SCHED_AMAX>);
+    case SCHED_AMIN: return reinterpret_cast<const void*>(&sk::k_tiny<SCHED_AMIN>);
+    case SCHED_HSF: return reinterpret_cast<const void*>(&sk::k_tiny<SCHED_HSF>);
+    case SCHED_AELL: return reinterpret_cast<const void*>(&sk::k_tiny<SCHED_AELL>);
+    case SCHED_ARANDOM: return reinterpret_cast<const void*>(&sk::k_tiny<SCHED_ARANDOM>);
+    default: return reinterpret_cast<const void*>(&sk::k_tiny<SCHED_ADAPTIVE>);
+  }
+}
+
 }  // namespace
 
 extern "C" {
@@ -565,26 +601,32 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
   const bool rounds = static_cast<int64_t>(K) > 16 * static_cast<int64_t>(n_cu);
   const bool ord = algo == SCHED_AMIN && in->total_requests > 0 && rounds;
   const size_t o_or = off; off = align_up(off + (ord ? 8 * K + 4 * sk::kOrderBuckets : 0), 256);
+  if (no_alloc && off > kScratchBytes) return SCHED_E_SCRATCH;
+  // tiny instances: one launch, a lane each, and no workspace (unless an option
+  // asks for a tier of the other kernels)
+  if (!ww && forced_rows == 0 && o.evicted_capacity == 0 && o.evicted_lds_limit == 0 &&
+      tiny_batch(nmax, in->num_instances, n_cu)) {
+    sk::Params P = result_params(in, M, out, o.step_cap);
+    hipError_t err = hipSuccess;
+    if (o.event_before) err = hipEventRecord(static_cast<hipEvent_t>(o.event_before), st);
+    if (err == hipSuccess) {
+      const dim3 tgrid((P.K + 63) / 64), tblock(64);
+      void* args[] = {&P};
+      err = hipLaunchKernel(tiny_kernel(algo), tgrid, tblock, args, 0, st);
+    }
+    if (err == hipSuccess && o.event_after) err = hipEventRecord(static_cast<hipEvent_t>(o.event_after), st);
+    return err == hipSuccess ? SCHED_OK : SCHED_E_HIP;
+  }
   // every workspace array is written before it is read (nothing needs clearing)
   void* ws = nullptr;
   if (no_alloc) {
-    if (off > kScratchBytes) return SCHED_E_SCRATCH;
     if (scratch_address(dev, &ws) != hipSuccess) return SCHED_E_HIP;
   } else if (hipMallocAsync(&ws, off, st) != hipSuccess) {
     return SCHED_E_HIP;
   }
   char* base = static_cast<char*>(ws);
 
-  sk::Params P = base_params(in, M);
-  P.completion = out->completion;
-  P.evictions = out->evictions;
-  P.total_latency = out->total_latency;
-  P.makespan = out->makespan;
-  P.request_steps = out->request_steps;
-  P.total_evictions = out->total_evictions;
-  P.status = out->status;
-  P.algo_used = out->algo_used;
-  P.step_cap = o.step_cap;
+  sk::Params P = result_params(in, M, out, o.step_cap);
   P.sort_a = reinterpret_cast<uint32_t*>(base + o_sa);
   P.sort_b = reinterpret_cast<uint32_t*>(base + o_sb);
   P.rec = reinterpret_cast<uint2*>(base + o_rec);
@@ -598,10 +640,12 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
   P.ev_st = tie && out->evictions ? reinterpret_cast<int32_t*>(base + o_es) : nullptr;
   P.vglob = any_global ? reinterpret_cast<uint64_t*>(base + o_vg) : nullptr;
   P.vgroup = group_words ? reinterpret_cast<uint64_t*>(base + o_gv) : nullptr;
-  P.pclass = pcl ? reinterpret_cast<int32_t*>(base + o_pc) : nullptr;
-  P.order = ord ? reinterpret_cast<int32_t*>(base + o_or) : nullptr;
-  P.okey = ord ? P.order + K : nullptr;
-  P.obucket = ord ? P.okey + K : nullptr;
+  // (only the ladder kernels read the classes and the order)
+  const bool ladder = tiers[0][0].grow;
+  P.pclass = pcl && ladder ? reinterpret_cast<int32_t*>(base + o_pc) : nullptr;
+  P.order = ord && ladder ? reinterpret_cast<int32_t*>(base + o_or) : nullptr;
+  P.okey = P.order ? P.order + K : nullptr;
+  P.obucket = P.order ? P.okey + K : nullptr;
   P.nw_max = nw;
   P.nw1_max = nw1;
   P.run_cap = forced_rows > 0 ? forced_rows * 64 : INT32_MAX;
