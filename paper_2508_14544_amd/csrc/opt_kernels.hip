@@ -42,6 +42,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "schedsim.h"
 
 namespace opt {
@@ -65,20 +67,24 @@ struct OptParams {
   int32_t* status;
   int64_t* nodes;
   int32_t unfinished;       // first launch: status of an instance not finished within node_cap
-  // second launch: [0] the number U of unfinished instances, then four arrays
-  // of K entries: the instances, their piece counters, best totals and flags
-  // (bit 0: every piece claimed; bit 1: a wave ran out of nodes)
+  // second launch: [0] the number U of unfinished instances, [1] how many of
+  // them do not fit a memory profile, then four arrays of K entries: the
+  // instances, their piece counters, best totals and flags (bit 0: every piece
+  // claimed; bit 1: a wave ran out of nodes; bit 2: does not fit a profile)
   int32_t* pool;
 };
 
-// status of an instance left to the second launch
-constexpr int kSplit = -100;
-// nodes of the first launch (one wave per instance)
+// statuses of an instance left to the second launch: kSplit searches it over a
+// memory profile, kSplitWide over the placed runs
+constexpr int kSplit = -100, kSplitWide = -101;
+// most nodes of the first launch (one wave per instance); a call with a budget
+// up to this has no second launch
 constexpr int64_t kFirstPassNodes = int64_t(1) << 17;
 // waves of a second-launch workgroup, and the depth below which they split
 constexpr int kGroupWaves = 16;
 constexpr int kSplitDepth = 2;
-constexpr int kFlagClaimed = 1, kFlagStop = 2;
+constexpr int kFlagClaimed = 1, kFlagStop = 2, kFlagWide = 4;
+constexpr int kPoolHead = 2;  // words of the pool before its arrays
 
 // One instance, sorted into search order.
 struct Inst {
@@ -167,6 +173,181 @@ __device__ __forceinline__ void wplace(const Inst& I, Search& S, int32_t cost, i
         if (S.stop) return;
       }
       if (lv != ~0ull) return;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The same search where every step that a run can reach fits the 64 lanes (the
+// horizon plus the longest run at most 63: any instance of the competitive-ratio
+// study).  Lane c holds the memory at step c of the runs placed so far, so the
+// starts that a request can take are one window maximum of mem(c) + c over its
+// length, compared with M (o shifts by a lane, two instructions each), instead of
+// a test per placed run (about eight each); placing a run is one masked add, and
+// nothing is undone: a level keeps the memory that it was given.  Tests, order,
+// pruning and the nodes counted in the first launch are those of wplace.  65536
+// instances of 8 requests (bounded by H-SF's totals): 112 ms a call, 459 ms with
+// the tests per placed run and a walk over every pair of first starts.
+// ---------------------------------------------------------------------------
+//
+// The bound needs one number a level: a node's cost plus the outputs still to
+// come is e, the sum of all outputs and of the waits p - a chosen so far, so a
+// start p is live while e + p - a < best, and a complete schedule costs its own e.
+constexpr int32_t kProfileSteps = 64;
+
+// One instance as the profile search reads it: few scalars, so that the levels'
+// own state stays in scalar registers.
+struct Slim {
+  int32_t a[kMaxN], o[kMaxN], s[kMaxN];
+  uint32_t same;
+  int n;
+  int32_t M, horizon;
+};
+
+__device__ __forceinline__ bool fits_profile(const Inst& I) {
+  int32_t omax = 0;
+#pragma unroll
+  for (int i = 0; i < kMaxN; ++i) omax = (i < I.n && I.o[i] > omax) ? I.o[i] : omax;
+  return I.horizon + omax < kProfileSteps;
+}
+
+__device__ __forceinline__ Slim slim(const Inst& I) {
+  Slim Q;
+#pragma unroll
+  for (int i = 0; i < kMaxN; ++i) {
+    Q.a[i] = I.a[i];
+    Q.o[i] = I.o[i];
+    Q.s[i] = I.s[i];
+  }
+  Q.same = I.same;
+  Q.n = I.n;
+  Q.M = I.M;
+  Q.horizon = I.horizon;
+  return Q;
+}
+
+// The starts (bits) at which a run of length o and prompt s keeps the memory
+// within M, given the memory at each step.  (Bits above 63 - o mean nothing.)
+__device__ __forceinline__ uint64_t profile_starts(int32_t mem, int32_t s, int32_t o, int32_t M) {
+  int32_t sh = mem, mx = mem;   // sh: mem(c + k) + k
+  // the shifted-in lane belongs to starts whose run leaves the 64 steps
+  auto next = [&]() {
+    sh = __builtin_amdgcn_update_dpp(0, sh, 0x130, 0xF, 0xF, true) + 1;
+    mx = sh > mx ? sh : mx;
+  };
+  next();   // o >= 1
+  if (o > 1) {
+    next();
+    if (o > 2) {
+      next();
+      if (o > 3) {
+        next();
+        if (o > 4) {
+          next();
+          if (o > 5) {
+            next();
+            for (int32_t k = 6; k < o; ++k) next();
+          }
+        }
+      }
+    }
+  }
+  return __builtin_amdgcn_ballot_w64(mx <= M - s);
+}
+
+// the memory with a run of length o and prompt s started at p
+__device__ __forceinline__ int32_t profile_with(int32_t mem, int32_t s, int32_t o, int32_t p, int lane) {
+  const int32_t d = lane - p;
+  return static_cast<uint32_t>(d) <= static_cast<uint32_t>(o) ? mem + d + s : mem;
+}
+
+// bits [lo, hi) (0 <= lo, hi <= 64)
+__device__ __forceinline__ uint64_t bit_span(int32_t lo, int32_t hi) {
+  return hi > lo ? (~0ull >> (64 - (hi - lo))) << lo : 0ull;
+}
+
+// wplace over the memory profile; pprev: the start of request D - 1.
+template <int D, bool SHARED>
+__device__ __forceinline__ void pplace(const Slim& I, Search& S, int32_t e, int32_t mem, int32_t pprev, int lane,
+                                       int32_t* sb) {
+  if constexpr (D < kMaxN) {
+    const bool last = D == I.n - 1;
+    const int32_t lo = (D > 0 && ((I.same >> D) & 1u)) ? pprev : I.a[D];
+    if (lo > I.horizon) return;
+    if constexpr (SHARED) {
+      if (!last) {
+        const int32_t g = __builtin_amdgcn_readfirstlane(
+            __hip_atomic_load(sb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+        S.best = g < S.best ? g : S.best;
+      }
+    }
+    const int32_t eb = e - I.a[D];
+    const int32_t lim = S.best - eb;
+    const int32_t hi = lim < I.horizon + 1 ? lim : I.horizon + 1;
+    const int32_t live = hi > lo ? hi - lo : 0;
+    S.nodes += live + 1;
+    if (S.nodes > S.cap) {
+      S.stop = true;
+      return;
+    }
+    if (live == 0) return;
+    uint64_t m = (((~0ull) >> (64 - live)) << lo) & profile_starts(mem, I.s[D], I.o[D], I.M);
+    if (m == 0ull) return;
+    if (last) {
+      S.best = eb + __builtin_ctzll(m);  // a complete schedule; later starts cost more
+      if constexpr (SHARED) {
+        if (lane == 0) atomicMin(sb, S.best);
+      }
+      return;
+    }
+    do {
+      const int32_t pj = __builtin_ctzll(m);
+      m &= m - 1;
+      if (eb + pj >= S.best) return;  // the bound improved below an earlier start
+      pplace<D + 1, SHARED>(I, S, eb + pj, profile_with(mem, I.s[D], I.o[D], pj, lane), pj, lane, sb);
+      if (S.stop) return;
+    } while (m);
+  }
+}
+
+// wtop over the memory profile (n > kSplitDepth = 2): the same leaves in the
+// same order; the starts of the second request are one mask, so the leaves of
+// a first start that are all claimed are passed by their number.
+__device__ __forceinline__ void ptop(const Slim& I, Search& S, int32_t e, int lane, int32_t* sb, int32_t* cnt,
+                                     int32_t* gb, int32_t claim) {
+  int32_t leaf = 0;
+  for (int32_t p0 = I.a[0]; p0 <= I.horizon; ++p0) {
+    const int32_t lo = ((I.same >> 1) & 1u) ? p0 : I.a[1];
+    S.nodes += 1 + (lo <= I.horizon ? I.horizon - lo + 1 : 0);
+    const int32_t mem0 = profile_with(0, I.s[0], I.o[0], p0, lane);
+    uint64_t m = bit_span(lo, I.horizon + 1) & profile_starts(mem0, I.s[1], I.o[1], I.M);
+    const int32_t here = __builtin_popcountll(m);
+    if (claim >= leaf + here) {
+      leaf += here;
+      continue;
+    }
+    while (m) {
+      const int32_t p1 = __builtin_ctzll(m);
+      m &= m - 1;
+      if (leaf == claim) {
+        const int32_t g = __builtin_amdgcn_readfirstlane(
+            __hip_atomic_load(sb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+        S.best = g < S.best ? g : S.best;
+        const int32_t e2 = e + (p0 - I.a[0]) + (p1 - I.a[1]);
+        if (e2 < S.best)
+          pplace<2, true>(I, S, e2, profile_with(mem0, I.s[1], I.o[1], p1, lane), p1, lane, sb);
+        int32_t nx = 0, gbv = 0;
+        if (lane == 0) {
+          nx = atomicAdd(cnt, 1);
+          gbv = atomicMin(gb, S.best);
+        }
+        claim = __builtin_amdgcn_readfirstlane(nx);
+        gbv = __builtin_amdgcn_readfirstlane(gbv);
+        if (gbv < S.best) S.best = gbv;
+        if (lane == 0) atomicMin(sb, S.best);
+        if (S.stop) return;
+      }
+      ++leaf;
     }
   }
 }
@@ -329,10 +510,11 @@ __global__ __launch_bounds__(64) void k_optimum(OptParams P) {
   Inst I;
   int status = setup(P, k, I, S);
   if (status == SCHED_OK && I.n > 0) {
-    wplace<0, false>(I, S, 0, lane, nullptr);
-    if (S.stop) status = P.unfinished;
+    if (fits_profile(I)) pplace<0, false>(slim(I), S, I.rem[0], 0, 0, lane, nullptr);
+    else wplace<0, false>(I, S, 0, lane, nullptr);
+    if (S.stop) status = P.unfinished == kSplit && !fits_profile(I) ? kSplitWide : P.unfinished;
   }
-  if (status != SCHED_OK && status != SCHED_E_STEP_CAP && status != kSplit) S.best = 0;
+  if (status != SCHED_OK && status != SCHED_E_STEP_CAP && status != kSplit && status != kSplitWide) S.best = 0;
   if (lane == 0) {
     P.total_latency[k] = S.best;
     P.status[k] = status;
@@ -343,18 +525,20 @@ __global__ __launch_bounds__(64) void k_optimum(OptParams P) {
 // Between the launches: the list of unfinished instances (in no particular
 // order) and their search state.  k_pool_reset clears the count first.
 __global__ __launch_bounds__(64) void k_pool_reset(OptParams P) {
-  if (threadIdx.x == 0) P.pool[0] = 0;
+  if (threadIdx.x < kPoolHead) P.pool[threadIdx.x] = 0;
 }
 
 __global__ __launch_bounds__(256) void k_pool_list(OptParams P) {
   const int k = blockIdx.x * 256 + static_cast<int>(threadIdx.x);
-  if (k >= P.K || P.status[k] != kSplit) return;
-  int32_t* list = P.pool + 1;
+  if (k >= P.K || (P.status[k] != kSplit && P.status[k] != kSplitWide)) return;
+  const bool wide = P.status[k] == kSplitWide;
+  int32_t* list = P.pool + kPoolHead;
   const int j = atomicAdd(P.pool, 1);
+  if (wide) atomicAdd(P.pool + 1, 1);
   list[j] = k;
   list[P.K + j] = 0;                                           // piece counter
   list[2 * P.K + j] = static_cast<int32_t>(P.total_latency[k]);  // best so far
-  list[3 * P.K + j] = 0;                                       // flags
+  list[3 * P.K + j] = wide ? kFlagWide : 0;                    // flags
 }
 
 // Second launch: workgroups of kGroupWaves waves, as many as the device holds
@@ -363,15 +547,18 @@ __global__ __launch_bounds__(256) void k_pool_list(OptParams P) {
 // claim and search pieces (wtop) until none is left, then meet at a barrier
 // and move on.  Each wave has at most P.node_cap nodes per instance it works
 // on; a wave that runs out marks the instance stopped (its result is then an
-// upper bound), and workgroups that come to it later skip it.
+// upper bound), and workgroups that come to it later skip it.  WIDE: the
+// instances that do not fit a memory profile; a kernel of its own, since its
+// search holds 128 vector registers where the other's fits twice as many waves.
+template <bool WIDE>
 __global__ __launch_bounds__(64 * kGroupWaves) void k_optimum_pool(OptParams P) {
   __shared__ int32_t sbest, sflag;
   const int U = P.pool[0];
-  if (U <= 0) return;
-  const int32_t* list = P.pool + 1;
-  int32_t* cnt = P.pool + 1 + P.K;
-  int32_t* gbest = P.pool + 1 + 2 * P.K;
-  int32_t* flags = P.pool + 1 + 3 * P.K;
+  if (U - (WIDE ? 0 : P.pool[1]) <= 0 || (WIDE && P.pool[1] <= 0)) return;
+  const int32_t* list = P.pool + kPoolHead;
+  int32_t* cnt = P.pool + kPoolHead + P.K;
+  int32_t* gbest = P.pool + kPoolHead + 2 * P.K;
+  int32_t* flags = P.pool + kPoolHead + 3 * P.K;
   const int lane = static_cast<int>(threadIdx.x & 63u);
   const int j0 = static_cast<int>((static_cast<int64_t>(blockIdx.x) * U) / gridDim.x);
   for (int step = 0; step < U; ++step) {
@@ -381,7 +568,7 @@ __global__ __launch_bounds__(64 * kGroupWaves) void k_optimum_pool(OptParams P) 
       sbest = __hip_atomic_load(&gbest[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (sflag == 0) {
+    if (sflag == (WIDE ? kFlagWide : 0)) {
       const int k = list[j];
       Search S;
       S.nodes = 0;
@@ -389,11 +576,13 @@ __global__ __launch_bounds__(64 * kGroupWaves) void k_optimum_pool(OptParams P) 
       S.stop = false;
       Inst I;
       (void)setup(P, k, I, S);  // valid: the first launch searched it
-      S.best = sbest;
+      S.best = __builtin_amdgcn_readfirstlane(sbest);
       int32_t first = 0;
       if (lane == 0) first = atomicAdd(&cnt[j], 1);
-      int32_t leaf = 0, claim = __builtin_amdgcn_readfirstlane(first);
-      wtop<0>(I, S, 0, lane, &sbest, &cnt[j], &gbest[j], leaf, claim);
+      [[maybe_unused]] int32_t leaf = 0;
+      int32_t claim = __builtin_amdgcn_readfirstlane(first);
+      if constexpr (WIDE) wtop<0>(I, S, 0, lane, &sbest, &cnt[j], &gbest[j], leaf, claim);
+      else ptop(slim(I), S, I.rem[0], lane, &sbest, &cnt[j], &gbest[j], claim);
       if (lane == 0) {
         atomicMin(&gbest[j], S.best);
         if (P.nodes) atomicAdd(reinterpret_cast<unsigned long long*>(&P.nodes[k]),
@@ -410,7 +599,7 @@ __global__ __launch_bounds__(64 * kGroupWaves) void k_optimum_pool(OptParams P) 
 __global__ __launch_bounds__(256) void k_pool_finish(OptParams P) {
   const int j = blockIdx.x * 256 + static_cast<int>(threadIdx.x);
   if (j >= P.pool[0]) return;
-  const int32_t* list = P.pool + 1;
+  const int32_t* list = P.pool + kPoolHead;
   const int k = list[j];
   P.total_latency[k] = list[2 * P.K + j];
   P.status[k] = (list[3 * P.K + j] & kFlagStop) ? SCHED_E_STEP_CAP : SCHED_OK;
@@ -442,20 +631,31 @@ extern "C" int sched_optimum(const sched_instances_t* in, int64_t M, const int64
   P.nodes = nodes;
   // a first launch with a short budget, then the unfinished instances on workgroups
   const bool split = cap > opt::kFirstPassNodes;
-  P.node_cap = split ? opt::kFirstPassNodes : cap;
+  P.node_cap = cap;
   P.unfinished = split ? opt::kSplit : SCHED_E_STEP_CAP;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   // the second launch's grid: as many workgroups as the device holds at once
-  int dev = 0, n_cu = 0, per_cu = 0;
+  int dev = 0, n_cu = 0, per_cu = 0, per_cu_wide = 0;
   if (split) {
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, opt::k_optimum_pool, 64 * opt::kGroupWaves, 0) !=
-            hipSuccess)
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, opt::k_optimum_pool<false>, 64 * opt::kGroupWaves, 0) !=
+            hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_wide, opt::k_optimum_pool<true>, 64 * opt::kGroupWaves,
+                                                     0) != hipSuccess)
       return SCHED_E_HIP;
+    // The first launch's budget: a wave takes about 55 ns a node, so where the
+    // device holds every instance at once (16 waves a CU) the launch lasts as
+    // long as the budget, and the second one, which searches on every CU, starts
+    // late; the more rounds of waves, the more a larger budget saves there.  8
+    // requests, budgets 2^12 and 2^17: 64 instances 0.93 and 7.0 ms, 4096 12.1
+    // and 15.3 ms, 65536 156 and 112 ms; 2000 of 7 requests 2.6 and 8.4 ms.
+    const int64_t rounds = (static_cast<int64_t>(P.K) + 16 * int64_t(n_cu) - 1) / (16 * int64_t(n_cu));
+    P.node_cap = std::min(opt::kFirstPassNodes, (int64_t(1) << 12) * (rounds <= 1 ? 1 : 2 * rounds));
     if (per_cu < 1) per_cu = 1;
-    // workspace: the count, then four arrays of K entries
-    if (hipMallocAsync(reinterpret_cast<void**>(&P.pool), sizeof(int32_t) * (1 + 4 * static_cast<size_t>(P.K)), st) !=
+    if (per_cu_wide < 1) per_cu_wide = 1;
+    // workspace: the counts, then four arrays of K entries
+    if (hipMallocAsync(reinterpret_cast<void**>(&P.pool), sizeof(int32_t) * (opt::kPoolHead + 4 * static_cast<size_t>(P.K)), st) !=
         hipSuccess)
       return SCHED_E_HIP;
   }
@@ -467,7 +667,8 @@ extern "C" int sched_optimum(const sched_instances_t* in, int64_t M, const int64
       hipLaunchKernelGGL(opt::k_pool_reset, dim3(1), dim3(64), 0, st, P);
       hipLaunchKernelGGL(opt::k_pool_list, g256, dim3(256), 0, st, P);
       P.node_cap = cap;
-      hipLaunchKernelGGL(opt::k_optimum_pool, dim3(n_cu * per_cu), dim3(64 * opt::kGroupWaves), 0, st, P);
+      hipLaunchKernelGGL(opt::k_optimum_pool<false>, dim3(n_cu * per_cu), dim3(64 * opt::kGroupWaves), 0, st, P);
+      hipLaunchKernelGGL(opt::k_optimum_pool<true>, dim3(n_cu * per_cu_wide), dim3(64 * opt::kGroupWaves), 0, st, P);
       hipLaunchKernelGGL(opt::k_pool_finish, g256, dim3(256), 0, st, P);
       err = hipGetLastError();
     }
