@@ -34,8 +34,9 @@
 // Both waiting sets thus offer their next candidates in lane order, and the
 // admissions of a step take them from there four at a time: one pass over the
 // rows and one transposed wave reduction give f at the planned ends of all four
-// (wave::sum4), and each admission is then one pass over the rows with new values
-// of f, one ballot, and the write of the run into its slot.
+// (wave::sum4).  When all four fit, one more pass gives the rows' new values of f
+// and one ballot admits them; else each admission is one pass over the rows with
+// new values of f, one ballot, and the write of the run into its slot.
 // The benchmark's A_min batch (4096 x 1000) took 10.9 ms and H-SF's sweep 33.7 ms
 // when every admission did a reduction, the head's search and the test's second
 // pass over the rows of its own.
@@ -73,6 +74,7 @@ struct WaveStateT {
   uint32_t vw_key, vw_so, pn_key, pn_so;
   int32_t v_lo, v_hi, v_sp, n_pend, n_ovf;
   int32_t q_head, q_n, q_base;
+  int32_t e_max, f_max;
   int32_t n_done, retry_at, t, DT;
   int64_t rsteps, tot_ev;
   int32_t next_rows;
@@ -96,7 +98,7 @@ __device__ __forceinline__ void fresh_state(ST& st) {
   st.f_base = -1; st.fw_u = 0; st.fw_key = 0xFFFFFFFFu; st.fw_so = 0; st.f_word = 0ull;
   st.vw_key = threadIdx.x < 32 ? 0u : 0xFFFFFFFFu; st.vw_so = 0; st.pn_key = 0xFFFFFFFFu; st.pn_so = 0;
   st.v_lo = 32; st.v_hi = 32; st.v_sp = 0; st.n_pend = 0; st.n_ovf = 0;
-  st.q_head = 0; st.q_n = 0; st.q_base = -(1 << 30);
+  st.q_head = 0; st.q_n = 0; st.q_base = -(1 << 30); st.e_max = 0; st.f_max = 0;
   st.n_done = 0; st.retry_at = 0; st.t = 0; st.DT = 0; st.rsteps = 0; st.tot_ev = 0;
   st.next_rows = 2; st.resume = false;
 }
@@ -126,6 +128,15 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
   constexpr bool kEarly = ALGO == SCHED_AMAX || ALGO == SCHED_AELL;
   // every run completes at its planned end
   constexpr bool kOnPlan = ALGO == SCHED_HSF || ALGO == SCHED_ARANDOM;
+  // Requests start in ascending planned length (but for arrivals), so a new run's
+  // planned end is usually the latest.  f at such an end is known without a pass
+  // over the rows and a wave reduction: with e_max and f_max kept, H-SF's sweep
+  // (65536 x 2000) went from 27.9 to 22.4 ms and one A_max instance of 100000 from
+  // 161 to 150 ms.
+  constexpr bool kSorted = ALGO == SCHED_HSF || ALGO == SCHED_AMAX;
+  // Four admissions in one test.  Not where each is cheap by itself and one in a few
+  // steps is the rule: H-SF's sweep took 44 ms with attempts that mostly failed.
+  constexpr bool kGroup = !kSorted;
   // nothing happens to the runs but their completions once nothing waits
   constexpr bool kDrains = kOnPlan || ALGO == SCHED_AMAX;
   extern __shared__ uint64_t lds64[];
@@ -225,6 +236,8 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
     uint32_t vw_key = lane < 32 ? 0u : 0xFFFFFFFFu, vw_so = 0, pn_key = 0xFFFFFFFFu, pn_so = 0;
     int32_t v_lo = 32, v_hi = 32, v_sp = 0, n_pend = 0, n_ovf = 0;
     int32_t q_head = 0, q_n = 0, q_base = -(1 << 30);
+    // kSorted: no run's planned end is above e_max, and f_max = f(e_max)
+    int32_t e_max = 0, f_max = 0;
     int32_t n_done = 0;
     int32_t retry_at = 0;         // the head cannot start before it; valid until the next event
     int32_t t = 0;
@@ -240,6 +253,9 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
       if constexpr (kAmin) {
         pn_key = st->pn_key; pn_so = st->pn_so; v_lo = st->v_lo; v_hi = st->v_hi; v_sp = st->v_sp;
         n_pend = st->n_pend; n_ovf = st->n_ovf;
+      }
+      if constexpr (kSorted) {
+        e_max = st->e_max; f_max = st->f_max;
       }
       if constexpr (kQueue) {
         fw_u = st->fw_u; q_head = st->q_head; q_n = st->q_n; q_base = st->q_base;
@@ -424,6 +440,9 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
       st->pn_key = pn_key; st->pn_so = pn_so; st->v_lo = v_lo; st->v_hi = v_hi;        \
       st->v_sp = v_sp; st->n_pend = n_pend; st->n_ovf = n_ovf;                         \
     }                                                                                  \
+    if constexpr (kSorted) {                                                           \
+      st->e_max = e_max; st->f_max = f_max;                                            \
+    }                                                                                  \
     if constexpr (kQueue) {                                                            \
       st->fw_u = fw_u; st->q_head = q_head; st->q_n = q_n; st->q_base = q_base;        \
     }                                                                                  \
@@ -521,8 +540,10 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
                 const int ln = __builtin_ctzll(mm);
                 mm &= mm - 1;
                 const int32_t ek = wave::readlane(r_end[r], ln);
+                const int32_t xk = wave::readlane(r_x[r], ln);
+                if (kSorted && ek == e_max) f_max -= xk - t_r + ek;
                 if (ek > t + 1) {
-                  SK_DROP_SHARE(wave::readlane(r_x[r], ln), ek);
+                  SK_DROP_SHARE(xk, ek);
                   retry_at = wave::in_sgpr(0);
                 }
               }
@@ -873,11 +894,20 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
         const int32_t dh = s - t;
         int32_t nf[ROWS];
         int32_t fmx = 0;
+        const bool top = kSorted && E >= e_max;   // no planned end is above E
+        if (top) {
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-          const bool in = static_cast<uint32_t>(r_end[r]) - lo2 < span;
-          nf[r] = in ? r_f[r] + r_end[r] + dh : r_f[r];
-          fmx = nf[r] > fmx ? nf[r] : fmx;
+          for (int r = 0; r < ROWS; ++r) {
+            nf[r] = r_end[r] > t + 1 ? r_f[r] + r_end[r] + dh : r_f[r];
+            fmx = nf[r] > fmx ? nf[r] : fmx;
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < ROWS; ++r) {
+            const bool in = static_cast<uint32_t>(r_end[r]) - lo2 < span;
+            nf[r] = in ? r_f[r] + r_end[r] + dh : r_f[r];
+            fmx = nf[r] > fmx ? nf[r] : fmx;
+          }
         }
         if (wave::ballot(fmx > M) != 0ull) {
           // each violating end improves by one per step, or leaves the window
@@ -892,36 +922,139 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
           wait_until = retry_at;
           goto admitted;
         }
-        if (q_at == 64) {
-          // planned length of each lane's candidate
-          const int32_t lest =
-              ALGO == SCHED_ARANDOM ? static_cast<int32_t>(bso >> 16) : static_cast<int32_t>(bkey >> kIdxBits);
-          uint64_t g = rest & (rest - 1ull);
-          int32_t e1 = kNever, e2 = kNever, e3 = kNever;
-          if (g != 0ull) {
-            e1 = t + wave::readlane(lest, __builtin_ctzll(g));
-            g &= g - 1ull;
+        int32_t fe;
+        if (top) {
+          fe = (E == e_max ? f_max : 0) + s + est;
+          q_at = 64;
+        } else {
+          if (q_at == 64) {
+            // planned length of each lane's candidate
+            const int32_t lest =
+                ALGO == SCHED_ARANDOM ? static_cast<int32_t>(bso >> 16) : static_cast<int32_t>(bkey >> kIdxBits);
+            uint64_t g = rest & (rest - 1ull);
+            int32_t e1 = kNever, e2 = kNever, e3 = kNever;
             if (g != 0ull) {
-              e2 = t + wave::readlane(lest, __builtin_ctzll(g));
+              e1 = t + wave::readlane(lest, __builtin_ctzll(g));
               g &= g - 1ull;
-              if (g != 0ull) e3 = t + wave::readlane(lest, __builtin_ctzll(g));
+              if (g != 0ull) {
+                e2 = t + wave::readlane(lest, __builtin_ctzll(g));
+                g &= g - 1ull;
+                if (g != 0ull) e3 = t + wave::readlane(lest, __builtin_ctzll(g));
+              }
+            }
+            ge = wave::writelane(ge, e1, 16);
+            ge = wave::writelane(ge, e2, 32);
+            ge = wave::writelane(ge, e3, 48);
+            int32_t fl0 = 0, fl1 = 0, fl2 = 0, fl3 = 0;
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+              fl0 = r_end[r] >= E ? fl0 + r_x[r] + (E - t_r) : fl0;
+              fl1 = r_end[r] >= e1 ? fl1 + r_x[r] + (e1 - t_r) : fl1;
+              fl2 = r_end[r] >= e2 ? fl2 + r_x[r] + (e2 - t_r) : fl2;
+              fl3 = r_end[r] >= e3 ? fl3 + r_x[r] + (e3 - t_r) : fl3;
+            }
+            gf = wave::sum4_i32(fl0, fl1, fl2, fl3);
+            q_at = 0;
+            if (kGroup && !CAPPED && e3 != kNever && __builtin_popcountll(fr_mask) >= 4) {
+              // The next three candidates with it, when their memory fits at t and
+              // t + 1 and the free row has room: the shares of all four on every row
+              // and on their own planned ends, and one test, which passes exactly
+              // when each would pass after those before it (shares only add).  When
+              // it does not pass, they are taken one by one, with the same sums.
+              // (A_min: 4096 x 1000 in 8.2 ms instead of 9.1, 65536 x 2000 in 109
+              // instead of 117; A_random 3000 x 1500 in 1.23 instead of 1.33; A_l
+              // 1024 x 10000 in 23.4 instead of 25.2.  Groups of two to four were
+              // slower than none on the last two.)
+              const uint64_t rest1 = rest & (rest - 1ull), rest2 = rest1 & (rest1 - 1ull), rest3 = rest2 & (rest2 - 1ull);
+              const int j1 = __builtin_ctzll(rest1), j2 = __builtin_ctzll(rest2), j3 = __builtin_ctzll(rest3);
+              const uint32_t so1 = wave::readlane_u(bso, j1), so2 = wave::readlane_u(bso, j2), so3 = wave::readlane_u(bso, j3);
+              const int32_t s1 = static_cast<int32_t>(so1 & 0xFFFFu), s2 = static_cast<int32_t>(so2 & 0xFFFFu);
+              const int32_t s3 = static_cast<int32_t>(so3 & 0xFFFFu);
+              const int32_t s4 = s + s1 + s2 + s3;
+              // (a run adds one less at t than at t + 1)
+              if ((Pm + 4 > at_t ? Pm + 4 : at_t) + s4 <= M) {
+                const int32_t d1 = s1 - t, d2 = s2 - t, d3 = s3 - t;
+                const uint32_t w1 = static_cast<uint32_t>(e1 - t - 1), w2 = static_cast<uint32_t>(e2 - t - 1);
+                const uint32_t w3 = static_cast<uint32_t>(e3 - t - 1);
+                int32_t gmx = 0;
+                int32_t ng[ROWS];
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) {
+                  const uint32_t c = static_cast<uint32_t>(r_end[r]) - lo2;
+                  ng[r] = c < w1 ? nf[r] + r_end[r] + d1 : nf[r];
+                  ng[r] = c < w2 ? ng[r] + r_end[r] + d2 : ng[r];
+                  ng[r] = c < w3 ? ng[r] + r_end[r] + d3 : ng[r];
+                  gmx = ng[r] > gmx ? ng[r] : gmx;
+                }
+                ge = wave::writelane(ge, E, 0);
+                int32_t f4 = gf;
+                f4 = ge <= E ? f4 + ge + dh : f4;
+                f4 = ge <= e1 ? f4 + ge + d1 : f4;
+                f4 = ge <= e2 ? f4 + ge + d2 : f4;
+                f4 = ge <= e3 ? f4 + ge + d3 : f4;
+                if ((wave::ballot(gmx > M) | (wave::ballot(f4 > M) & 0x0001000100010001ull)) == 0ull) {
+#pragma unroll
+                  for (int r = 0; r < ROWS; ++r) r_f[r] = ng[r];
+                  const uint64_t m1 = fr_mask & (fr_mask - 1ull), m2 = m1 & (m1 - 1ull), m3 = m2 & (m2 - 1ull);
+                  const int l0 = __builtin_ctzll(fr_mask), l1 = __builtin_ctzll(m1), l2 = __builtin_ctzll(m2);
+                  const int l3 = __builtin_ctzll(m3);
+                  const int32_t f0 = wave::readlane(f4, 0), f1 = wave::readlane(f4, 16);
+                  const int32_t f2 = wave::readlane(f4, 32), f3 = wave::readlane(f4, 48);
+                  const int32_t xb = t_r - t;
+                  const int32_t o1 = static_cast<int32_t>(so1 >> 16), o2 = static_cast<int32_t>(so2 >> 16);
+                  const int32_t o3 = static_cast<int32_t>(so3 >> 16);
+                  const uint32_t k1 = wave::readlane_u(bkey, j1), k2 = wave::readlane_u(bkey, j2), k3 = wave::readlane_u(bkey, j3);
+                  int32_t u0 = 0, u1 = 0, u2 = 0, u3 = 0;
+                  if (kQueue) {
+                    u0 = fromF ? wave::readlane(fw_u, j) : est;
+                    u1 = fromF ? wave::readlane(fw_u, j1) : e1 - t;
+                    u2 = fromF ? wave::readlane(fw_u, j2) : e2 - t;
+                    u3 = fromF ? wave::readlane(fw_u, j3) : e3 - t;
+                  }
+#define SK_PUT(LN_, E_, S_, O_, K_, F_, U_)                                          \
+  r_end[r] = wave::writelane(r_end[r], E_, LN_);                                     \
+  r_x[r] = wave::writelane(r_x[r], xb + S_, LN_);                                    \
+  r_c[r] = wave::writelane(r_c[r], t + O_, LN_);                                     \
+  r_key[r] = wave::writelane_u(r_key[r], K_, LN_);                                   \
+  r_f[r] = wave::writelane(r_f[r], F_, LN_);                                         \
+  if (kQueue) r_u[r] = wave::writelane(r_u[r], U_, LN_);
+                  SK_AT_ROW(fr_row, SK_PUT(l0, E, s, c_o, c_key, f0, u0) SK_PUT(l1, e1, s1, o1, k1, f1, u1)
+                            SK_PUT(l2, e2, s2, o2, k2, f2, u2) SK_PUT(l3, e3, s3, o3, k3, f3, u3))
+#undef SK_PUT
+                  fr_mask = m3 & (m3 - 1ull);
+                  int32_t near = c_o < o1 ? c_o : o1;
+                  near = o2 < near ? o2 : near;
+                  near = o3 < near ? o3 : near;
+                  if (kQueue) {
+                    near = est < near ? est : near;
+                    near = e1 - t < near ? e1 - t : near;
+                    near = e2 - t < near ? e2 - t : near;
+                    near = e3 - t < near ? e3 - t : near;
+                  }
+                  next_c = t + near < next_c ? t + near : next_c;
+                  X += s4 + 4 * xb;
+                  N += 4;
+                  Pm += s4 + 4;
+                  rest = rest3 & (rest3 - 1ull);
+                  if (kAmin && !fromF) {
+                    v_lo += 4;
+                    vw_key = lane < v_lo ? 0u : vw_key;
+                  } else if (kQueue && !fromF) {
+                    q_head += 4;
+                    q_n -= 4;
+                  } else {
+                    f_word &= ~1ull << j3;
+                  }
+                  retry_at = wave::in_sgpr(0);
+                  q_at = 64;
+                  mode = kNext;
+                  continue;
+                }
+              }
             }
           }
-          ge = wave::writelane(ge, e1, 16);
-          ge = wave::writelane(ge, e2, 32);
-          ge = wave::writelane(ge, e3, 48);
-          int32_t fl0 = 0, fl1 = 0, fl2 = 0, fl3 = 0;
-#pragma unroll
-          for (int r = 0; r < ROWS; ++r) {
-            fl0 = r_end[r] >= E ? fl0 + r_x[r] + (E - t_r) : fl0;
-            fl1 = r_end[r] >= e1 ? fl1 + r_x[r] + (e1 - t_r) : fl1;
-            fl2 = r_end[r] >= e2 ? fl2 + r_x[r] + (e2 - t_r) : fl2;
-            fl3 = r_end[r] >= e3 ? fl3 + r_x[r] + (e3 - t_r) : fl3;
-          }
-          gf = wave::sum4_i32(fl0, fl1, fl2, fl3);
-          q_at = 0;
+          fe = wave::readlane(gf, q_at) + s + est;
         }
-        const int32_t fe = wave::readlane(gf, q_at) + s + est;
         if (SK_RARE(est > 1 && fe > M)) {
           // f at the sliding end only grows until it passes the next planned end
           int32_t emin = kNever;
@@ -974,11 +1107,16 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
           next_c = ew < next_c ? ew : next_c;
           X += xw;
         }
-        // the later candidates of the four whose end it reaches
-        gf = ge <= E ? gf + ge + dh : gf;
+        if (kSorted && top) {
+          e_max = E;
+          f_max = fe;
+        } else {
+          // the later candidates of the four whose end it reaches
+          gf = ge <= E ? gf + ge + dh : gf;
+          q_at += 16;
+        }
         N += 1;
         Pm += s + 1;
-        q_at += 16;
         rest &= rest - 1ull;
         if (kAmin && !fromF) {
           vw_key = wave::writelane_u(vw_key, 0u, j);
