@@ -13,6 +13,7 @@ SOURCES = [os.path.join(PKG, "csrc", f) for f in
             "sched_wave_arandom.hip", "sched_wide.hip", "sched_group.hip", "sched_kernels.hip", "opt_kernels.hip")]
 HEADERS = [os.path.join(PKG, "csrc", "wave.hpp"), os.path.join(PKG, "csrc", "sim_device.hpp"),
            os.path.join(PKG, "csrc", "sim_wave.hpp"), os.path.join(PKG, "csrc", "sim_tiny.hpp"),
+           os.path.join(PKG, "csrc", "prepare.hpp"),
            os.path.join(ROOT, "include", "schedsim.h")]
 # throughput probes for the roofline (measurement infrastructure, own library)
 PROBE_LIB = os.path.join(PKG, "libschedprobe.so")

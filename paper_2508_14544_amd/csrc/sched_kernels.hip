@@ -4,6 +4,7 @@
 // row ladder (sched_wide.hip) and the workgroup kernels (sched_group.hip) are
 // translation units of their own.  The device code is in sim_wave.hpp and
 // sim_device.hpp.
+#include "prepare.hpp"
 #include "sim_tiny.hpp"
 #include "sim_wave.hpp"
 
@@ -42,6 +43,16 @@ extern template __global__ void k_simulate_group<SCHED_AMIN, 4, 4, true>(Params)
 extern template __global__ void k_simulate_group<SCHED_AMIN, 4, 16, false>(Params);
 extern template __global__ void k_simulate_group<SCHED_AMIN, 4, 16, true>(Params);
 extern template __global__ void k_simulate_group<SCHED_AMIN, 8, 16, true>(Params);
+
+// One wave an instance that sleeps until all of them have started (about 2 us).  A
+// CU gives a new wave the SIMD that follows the last one's, as long as waves end in the
+// order in which they came: after a kernel whose workgroups have several waves, or come
+// one after the other for lack of LDS, the CU's next four waves may share SIMDs (3 to 10
+// in 100 of 1024 waves on 256 CUs did, none after this kernel).  A simulation lasts as
+// long as its slowest instance, and a wave that shares its SIMD is slower: 1024 x 10000
+// A_l took 26.9 ms instead of 22.9, A_min 27.0 instead of 24.1.  Needed where a CU gets
+// more than two waves (with two none met) and all are resident at once.
+__global__ __launch_bounds__(64) void k_spread() { __builtin_amdgcn_s_sleep(64); }
 
 // Issue-priority classes (A_min with upper bounds, from k_prepare): kept only
 // where they differ between the instances of the batch; a batch whose
@@ -214,6 +225,42 @@ const void* sim_kernel(const Tier& tr, bool ordered, bool classes, bool rounds) 
     case 8: return reinterpret_cast<const void*>(&sk::k_simulate<ALGO, 8, false>);
     default: return reinterpret_cast<const void*>(&sk::k_simulate<ALGO, 16, false>);
   }
+}
+
+// The preparation's kernel, its waves an instance and its dynamic LDS.
+struct PrepareLaunch {
+  const void* kernel;
+  int waves;
+  size_t lds;
+  bool spread;  // k_spread has to follow
+};
+
+template <int W, bool LDS>
+const void* prepare_kernel(int algo) {
+  switch (algo) {
+    case SCHED_AMAX: return reinterpret_cast<const void*>(sk::k_prepare<SCHED_AMAX, W, LDS>);
+    case SCHED_AMIN: return reinterpret_cast<const void*>(sk::k_prepare<SCHED_AMIN, W, LDS>);
+    case SCHED_HSF: return reinterpret_cast<const void*>(sk::k_prepare<SCHED_HSF, W, LDS>);
+    case SCHED_AELL: return reinterpret_cast<const void*>(sk::k_prepare<SCHED_AELL, W, LDS>);
+    case SCHED_ARANDOM: return reinterpret_cast<const void*>(sk::k_prepare<SCHED_ARANDOM, W, LDS>);
+    default: return reinterpret_cast<const void*>(sk::k_prepare<SCHED_ADAPTIVE, W, LDS>);
+  }
+}
+
+// One wave an instance where it is one or a few chunks of 64 requests (with more
+// waves, most of them would wait at barriers), else four while an instance's buffers let
+// a CU hold several workgroups of them, else sixteen.  Measured, with 1 / 4 / 16
+// waves an instance: 65536 x 2000 2.32 / 1.45 / 3.84 ms, 1024 x 10000 0.79 / 0.43 /
+// 0.27 ms, 3000 x 1500 with tie keys 173 / 87 / 325 us, 4096 x 1000 58 / 50 / 192 us.
+PrepareLaunch prepare_launch(int algo, int64_t nmax, int64_t K, int n_cu, bool tie, int lds_max) {
+  // A_l sorts nothing but tie keys
+  const size_t lds = (tie ? 12 : algo == SCHED_AELL ? 4 : 8) * static_cast<size_t>(std::max<int64_t>(nmax, 1));
+  if (nmax <= 64 || (nmax <= 256 && K > 2 * int64_t(n_cu))) return {prepare_kernel<1, true>(algo), 1, lds, false};
+  const bool spread = K > 2 * int64_t(n_cu) && K <= 16 * int64_t(n_cu);
+  if (nmax <= 4096) return {prepare_kernel<4, true>(algo), 4, lds, spread};
+  if (lds + sizeof(sk::PrepareShared<16>) <= static_cast<size_t>(lds_max))
+    return {prepare_kernel<16, true>(algo), 16, lds, spread};
+  return {prepare_kernel<16, false>(algo), 16, 0, spread};
 }
 
 // ordered: A_min's narrow ladder takes the instances in the order P.order;
@@ -651,21 +698,17 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
   P.run_cap = forced_rows > 0 ? forced_rows * 64 : INT32_MAX;
 
   hipError_t err = hipSuccess;
-  const dim3 grid(P.K), block(64);
-  // the preparation's key sort in LDS (two buffers of n_max keys) when they
-  // take at most 32 KiB; with tie keys its index sorts use the workspace
-  P.pre_lds = (!tie && algo != SCHED_AELL && 8 * nmax <= 32768) ? 1 : 0;
-  const size_t pre_bytes = P.pre_lds ? 8 * static_cast<size_t>(nmax) : 0;
   if (P.order) hipLaunchKernelGGL(sk::k_order_clear, dim3(1), dim3(sk::kOrderBuckets), 0, st, P);
-  switch (algo) {
-    case SCHED_AMAX: hipLaunchKernelGGL((sk::k_prepare<SCHED_AMAX>), grid, block, pre_bytes, st, P); break;
-    case SCHED_AMIN: hipLaunchKernelGGL((sk::k_prepare<SCHED_AMIN>), grid, block, pre_bytes, st, P); break;
-    case SCHED_HSF: hipLaunchKernelGGL((sk::k_prepare<SCHED_HSF>), grid, block, pre_bytes, st, P); break;
-    case SCHED_AELL: hipLaunchKernelGGL((sk::k_prepare<SCHED_AELL>), grid, block, pre_bytes, st, P); break;
-    case SCHED_ARANDOM: hipLaunchKernelGGL((sk::k_prepare<SCHED_ARANDOM>), grid, block, pre_bytes, st, P); break;
-    default: hipLaunchKernelGGL((sk::k_prepare<SCHED_ADAPTIVE>), grid, block, pre_bytes, st, P); break;
+  {
+    const PrepareLaunch pl = prepare_launch(algo, nmax, in->num_instances, n_cu, tie, lds_max);
+    // (above 64 KiB a kernel's LDS has to be asked for)
+    if (pl.lds > 49152)
+      err = hipFuncSetAttribute(pl.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(pl.lds));
+    void* args[] = {&P};
+    if (err == hipSuccess) err = hipLaunchKernel(pl.kernel, dim3(P.K), dim3(64 * pl.waves), args, pl.lds, st);
+    if (pl.spread) hipLaunchKernelGGL(sk::k_spread, dim3(P.K), dim3(64), 0, st);
   }
-  err = hipGetLastError();
+  if (err == hipSuccess) err = hipGetLastError();
   if (err == hipSuccess && P.pclass) {
     hipLaunchKernelGGL(sk::k_prio_classes, dim3(1), dim3(256), 0, st, P);
     err = hipGetLastError();

@@ -134,10 +134,14 @@ struct Params {
   int32_t* order;
   int32_t* okey;
   int32_t* obucket;
-  // k_prepare: nonzero when its key sort runs in two LDS buffers of
-  // max_requests entries (dynamic LDS) instead of sort_a / sort_b
-  int32_t pre_lds;
 };
+
+// Whether some request of the instance of n > 0 requests from b on arrives after
+// step 0 (arrivals do not decrease).  Where none does, every rank waits from the
+// start, and k_prepare writes no rank_of.
+__device__ __forceinline__ bool late_arrivals(const Params& P, const int64_t b, const int n) {
+  return P.arrival && P.arrival[b + n - 1] > 0;
+}
 
 // buckets of the launch-order key
 constexpr int kOrderBuckets = 64;
@@ -147,331 +151,6 @@ constexpr int kOrderBuckets = 64;
 // later pass simulates it again from step 0 with more room.
 constexpr int kRetryRows = -100;
 constexpr int kRetryV = -101;
-
-// ---------------------------------------------------------------------------
-// k_prepare
-// ---------------------------------------------------------------------------
-// One stable LSD radix pass of a wave over the n elements src[0..n) -> dst,
-// by the 8-bit digit dig(element): LDS histogram, wave scan of the bucket
-// starts, and a stable scatter that ranks equal digits inside each 64-element
-// chunk with 8 ballots.
-template <typename DigitFn>
-__device__ __forceinline__ void radix_pass(uint32_t* hist, const uint32_t* src, uint32_t* dst, int n, DigitFn dig) {
-  const int lane = threadIdx.x;
-  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int j = lane; j < 256; j += 64) hist[j] = 0;
-  __syncthreads();
-  for (int c = 0; c < n; c += 64) {
-    const int i = c + lane;
-    if (i < n) atomicAdd(&hist[dig(src[i])], 1u);
-  }
-  __syncthreads();
-  {
-    uint32_t h0 = hist[4 * lane], h1 = hist[4 * lane + 1], h2 = hist[4 * lane + 2], h3 = hist[4 * lane + 3];
-    int32_t tot = static_cast<int32_t>(h0 + h1 + h2 + h3);
-    int32_t ex = wave::inclusive_scan_i32(tot) - tot;
-    __syncthreads();
-    hist[4 * lane] = ex;
-    hist[4 * lane + 1] = ex + h0;
-    hist[4 * lane + 2] = ex + h0 + h1;
-    hist[4 * lane + 3] = ex + h0 + h1 + h2;
-  }
-  __syncthreads();
-  for (int c = 0; c < n; c += 64) {
-    const int i = c + lane;
-    const bool act = i < n;
-    const uint32_t key = act ? src[i] : 0u;
-    const uint32_t d = act ? dig(key) : 0u;
-    uint64_t eq = wave::ballot(act);
-    for (int bit = 0; bit < 8; ++bit) {
-      const uint64_t bal = wave::ballot(act && ((d >> bit) & 1u));
-      eq &= ((d >> bit) & 1u) ? bal : ~bal;
-    }
-    const int rank = __builtin_popcountll(eq & lt_mask);
-    const uint32_t base = act ? hist[d] : 0u;
-    __syncthreads();
-    if (act) {
-      dst[base + rank] = key;
-      if (rank == 0) hist[d] = base + static_cast<uint32_t>(__builtin_popcountll(eq));
-    }
-    __syncthreads();
-  }
-  __syncthreads();
-}
-
-// Stable sort of the request indices 0..n-1 by the 32-bit key key(i) (four
-// radix passes; a byte on which every key agrees is skipped).  Returns the
-// buffer holding the sorted indices (a or b).
-template <typename KeyFn>
-__device__ __forceinline__ uint32_t* sort_indices_by(uint32_t* hist, uint32_t* a, uint32_t* b, int n, KeyFn key,
-                                                     bool init) {
-  const int lane = threadIdx.x;
-  uint32_t kand = 0xFFFFFFFFu, kor = 0u;
-  for (int c = 0; c < n; c += 64) {
-    const int i = c + lane;
-    if (i < n) {
-      if (init) a[i] = static_cast<uint32_t>(i);
-      const uint32_t k = key(static_cast<uint32_t>(i));
-      kand &= k;
-      kor |= k;
-    }
-  }
-  for (int off = 32; off >= 1; off >>= 1) {
-    kand &= static_cast<uint32_t>(__shfl_xor(static_cast<int>(kand), off, 64));
-    kor |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(kor), off, 64));
-  }
-  const uint32_t varies = kand ^ kor;
-  __syncthreads();
-  for (int pass = 0; pass < 4; ++pass) {
-    const int sh = 8 * pass;
-    if (((varies >> sh) & 0xFFu) == 0u) continue;
-    radix_pass(hist, a, b, n, [&](uint32_t e) { return (key(e) >> sh) & 0xFFu; });
-    uint32_t* t = a;
-    a = b;
-    b = t;
-  }
-  return a;
-}
-
-// Per-instance validation (shared by k_prepare and k_validate): the status
-// and, through *algo_out, the policy the instance runs (the adaptive choice);
-// also the default step cap.
-template <int ALGO>
-__device__ __forceinline__ int validate_instance(const Params& P, int k, int* algo_out, int64_t* cap_out) {
-  const int lane = threadIdx.x;
-  const int64_t b = P.offsets[k];
-  const int64_t e = P.offsets[k + 1];
-  int status = SCHED_OK;
-  if (b < 0 || e < b || e > P.N || e - b > P.max_requests) status = SCHED_E_INVAL;
-  const int n = (status == SCHED_OK) ? static_cast<int>(e - b) : 0;
-
-  // l is read by A_min and A_l, u by A_max and A_l; the adaptive policy reads
-  // both (their sums pick the policy) and validates with the one it picks
-  constexpr bool kReadL = ALGO == SCHED_AMIN || ALGO == SCHED_AELL || ALGO == SCHED_ADAPTIVE;
-  constexpr bool kReadU = ALGO == SCHED_AMAX || ALGO == SCHED_AELL || ALGO == SCHED_ADAPTIVE;
-  constexpr bool kReadP = ALGO == SCHED_ARANDOM;
-  bool arr_bad = false, int_bad = false, big_bad = false, unsup = (n >= (1 << kIdxBits));
-  bool bad_l = false, unsup_l = false, bad_u = false, big_u = false, unsup_u = false;
-  int64_t max_a = 0, sum_o = 0, sum_l = 0, sum_u = 0;
-  int32_t prev_last = 0;
-  for (int c = 0; c < n; c += 64) {
-    const int i = c + lane;
-    const bool act = i < n;
-    int32_t a = 0, s = 0, o = 1, lo = 1, up = 1, pr = 0;
-    if (act) {
-      a = P.arrival ? P.arrival[b + i] : 0;
-      s = P.prompt[b + i];
-      o = P.output[b + i];
-      if (kReadL) lo = P.lower[b + i];
-      if (kReadU) up = P.upper[b + i];
-      if (kReadP) pr = P.priority[b + i];
-    }
-    int32_t ap = __shfl_up(a, 1, 64);
-    if (lane == 0) ap = prev_last;
-    prev_last = __shfl(a, 63, 64);
-    if (act) {
-      if (a < 0 || (i > 0 && a < ap)) arr_bad = true;
-      if (o < 1 || s < 0) int_bad = true;
-      if (lo < 1 || lo > o) bad_l = true;
-      if (up < o) bad_u = true;
-      if (static_cast<int64_t>(s) + o > P.M) big_bad = true;
-      if (static_cast<int64_t>(s) + up > P.M) big_u = true;
-      if (o >= kEstLimit || s >= kPromptLimit || pr < 0 || pr >= kEstLimit) unsup = true;
-      if (lo >= kEstLimit) unsup_l = true;
-      if (up >= kEstLimit) unsup_u = true;
-      max_a = a > max_a ? a : max_a;
-      sum_o += static_cast<int64_t>(o) + 1;
-      sum_l += lo;
-      sum_u += up;
-    }
-  }
-  // the policy this instance runs; the adaptive one takes A_l when
-  // L/U < (3 - sqrt 5)/2, i.e. sqrt(5) U < 3U - 2L, i.e. 5U^2 < (3U - 2L)^2
-  int algo = ALGO;
-  if (ALGO == SCHED_ADAPTIVE) {
-    const int64_t L = wave::sum_i64(sum_l), U = wave::sum_i64(sum_u);
-    const int64_t d = 3 * U - 2 * L;
-    algo = SCHED_AMIN;
-    if (n > 0 && d > 0) {
-      const unsigned __int128 dd = static_cast<unsigned __int128>(d) * static_cast<unsigned __int128>(d);
-      const unsigned __int128 uu = static_cast<unsigned __int128>(U) * static_cast<unsigned __int128>(U);
-      if (dd > 5 * uu) algo = SCHED_AELL;
-    }
-  }
-  const bool use_l = algo == SCHED_AMIN || algo == SCHED_AELL;
-  const bool use_u = algo == SCHED_AMAX || algo == SCHED_AELL;
-  int_bad = int_bad || (use_l && bad_l) || (use_u && bad_u);
-  big_bad = big_bad || (use_u && big_u);
-  unsup = unsup || (use_l && unsup_l) || (use_u && unsup_u);
-  if (status == SCHED_OK) {
-    if (wave::ballot(arr_bad)) status = SCHED_E_ARRIVAL;
-    else if (wave::ballot(int_bad)) status = SCHED_E_INTERVAL;
-    else if (wave::ballot(big_bad)) status = SCHED_E_TOO_BIG;
-    else if (wave::ballot(unsup)) status = SCHED_E_UNSUPPORTED;
-  }
-  const int64_t max_a_all = wave::max_i64(max_a);
-  const int64_t sum_o_all = wave::sum_i64(sum_o);
-  int64_t cap = P.step_cap > 0 ? P.step_cap : 4 * (max_a_all + sum_o_all) + 64;
-  if (cap > kCapLimit) cap = kCapLimit;
-  *algo_out = algo;
-  *cap_out = cap;
-  return status;
-}
-
-// Validation only (sched_validate): status per instance.
-template <int ALGO>
-__global__ __launch_bounds__(64) void k_validate(Params P) {
-  const int k = blockIdx.x;
-  int algo = ALGO;
-  int64_t cap = 0;
-  const int status = validate_instance<ALGO>(P, k, &algo, &cap);
-  if (threadIdx.x == 0) {
-    P.status[k] = status;
-    if (P.algo_used) P.algo_used[k] = algo;
-  }
-}
-
-template <int ALGO>
-__global__ __launch_bounds__(64) void k_prepare(Params P) {
-  __shared__ uint32_t hist[256];
-  const int k = blockIdx.x;
-  const int lane = threadIdx.x;
-  int algo = ALGO;
-  int64_t cap = 0;
-  const int status = validate_instance<ALGO>(P, k, &algo, &cap);
-  const int64_t b = P.offsets[k];
-  const int n = (status == SCHED_OK) ? static_cast<int>(P.offsets[k + 1] - b) : 0;
-  const bool tie = P.tie_key != nullptr;
-
-  // per-request outputs start as "not completed, never cancelled" (with tie
-  // keys, the staging arrays the kernels write too)
-  const int64_t e = P.offsets[k + 1];
-  const int n_init = (b >= 0 && e > b && e <= P.N && e - b <= P.max_requests) ? static_cast<int>(e - b) : 0;
-  for (int c = 0; c < n_init; c += 64) {
-    const int i = c + lane;
-    if (i < n_init) {
-      P.completion[b + i] = -1;
-      if (P.evictions) P.evictions[b + i] = 0;
-      if (tie) {
-        P.comp_st[b + i] = -1;
-        if (P.evictions) P.ev_st[b + i] = 0;
-      }
-    }
-  }
-  if (lane == 0) {
-    P.status[k] = status;
-    P.cap[k] = static_cast<int32_t>(cap);
-    if (P.algo_of) P.algo_of[k] = algo;
-    if (P.algo_used) P.algo_used[k] = algo;
-    if (P.pclass) P.pclass[k] = 3;
-    if (P.okey && (status != SCHED_OK || n == 0)) {
-      P.okey[k] = 0;
-      atomicAdd(&P.obucket[0], 1);
-    }
-  }
-  if (status != SCHED_OK || n == 0) return;
-  if (P.pclass && algo == SCHED_AMIN) {
-    // wide intervals mean more cancellations, so longer simulations: the
-    // class by sum(u - l) / sum(l) (< 0.3, < 0.75, above)
-    int64_t w = 0, l = 0;
-    for (int c = 0; c < n; c += 64) {
-      const int i = c + lane;
-      if (i < n) {
-        w += P.upper[b + i] - P.lower[b + i];
-        l += P.lower[b + i];
-      }
-    }
-    w = wave::sum_i64(w);
-    l = wave::sum_i64(l);
-    if (lane == 0) P.pclass[k] = 4 * w >= 3 * l ? 2 : 10 * w >= 3 * l ? 1 : 0;
-  }
-  if (P.okey) {
-    // A_min cancels until its lower bounds have grown to the true lengths, so
-    // the instances whose lower bounds fall furthest below them run longest:
-    // the key is 16 * sum(o - l) / sum(l), at most kOrderBuckets - 1
-    int64_t w = 0, l = 0;
-    for (int c = 0; c < n; c += 64) {
-      const int i = c + lane;
-      if (i < n) {
-        w += P.output[b + i] - P.lower[b + i];
-        l += P.lower[b + i];
-      }
-    }
-    w = wave::sum_i64(w);
-    l = wave::sum_i64(l);
-    if (lane == 0) {
-      const int64_t q = l > 0 ? (16 * w) / l : 0;
-      const int key = q < kOrderBuckets - 1 ? static_cast<int>(q) : kOrderBuckets - 1;
-      P.okey[k] = key;
-      atomicAdd(&P.obucket[key], 1);
-    }
-  }
-
-  // ---- tie keys: each request's rank in the order (tie key, index) (A_l:
-  // (arrival, tie key, index), its fresh-queue order) is its identity in the
-  // keys below; tr_of maps index -> rank, idx_of rank -> index
-  if (tie) {
-    const int32_t* tk = P.tie_key + b;
-    uint32_t* S = sort_indices_by(hist, P.sort_a + b, P.sort_b + b, n,
-                                  [&](uint32_t i) { return static_cast<uint32_t>(tk[i]) ^ 0x80000000u; }, true);
-    if (algo == SCHED_AELL && P.arrival) {
-      const int32_t* ar = P.arrival + b;
-      uint32_t* other = S == P.sort_a + b ? P.sort_b + b : P.sort_a + b;
-      S = sort_indices_by(hist, S, other, n, [&](uint32_t i) { return static_cast<uint32_t>(ar[i]); }, false);
-    }
-    for (int c = 0; c < n; c += 64) {
-      const int r = c + lane;
-      if (r < n) {
-        const uint32_t i = S[r];
-        P.tr_of[b + i] = r;
-        P.idx_of[b + r] = static_cast<int32_t>(i);
-      }
-    }
-    __syncthreads();
-  }
-
-  // ---- keys (k0 << 17 | id), k0 = u (A_max), l (A_min, A_l), o (H-SF), the
-  // priority (A_random, which plans with o); id = the index, or the tie rank,
-  // placed at position id so that the stable sort below keeps id order.  The
-  // two sort buffers are in LDS when the launch gave them room (P.pre_lds)
-  extern __shared__ uint32_t pre_buf[];
-  uint32_t* const ka = P.pre_lds ? pre_buf : P.sort_a + b;
-  uint32_t* const kb = P.pre_lds ? pre_buf + P.max_requests : P.sort_b + b;
-  for (int c = 0; c < n; c += 64) {
-    const int i = c + lane;
-    if (i < n) {
-      int32_t est = (algo == SCHED_AMAX)   ? P.upper[b + i]
-                    : (algo == SCHED_HSF)  ? P.output[b + i]
-                    : (algo == SCHED_ARANDOM) ? P.priority[b + i]
-                                           : P.lower[b + i];
-      const uint32_t id = tie ? static_cast<uint32_t>(P.tr_of[b + i]) : static_cast<uint32_t>(i);
-      ka[id] = (static_cast<uint32_t>(est) << kIdxBits) | id;
-    }
-  }
-  __syncthreads();
-  // ---- stable LSD radix sort on bits 17..24 then 25..31 (A_l's queue is in
-  // id order: its ranks are the ids, no sort)
-  for (int pass = 0; pass < (algo == SCHED_AELL ? 0 : 2); ++pass) {
-    const uint32_t* src = pass == 0 ? ka : kb;
-    uint32_t* dst = pass == 0 ? kb : ka;
-    const int shift = kIdxBits + 8 * pass;
-    radix_pass(hist, src, dst, n, [&](uint32_t key) { return (key >> shift) & 0xFFu; });
-  }
-  // ---- ranked records and inverse ranks (rank_of is indexed by request index)
-  for (int c = 0; c < n; c += 64) {
-    const int r = c + lane;
-    if (r < n) {
-      const uint32_t key = ka[r];
-      const uint32_t id = key & kIdxMask;
-      const uint32_t idx = tie ? static_cast<uint32_t>(P.idx_of[b + id]) : id;
-      const uint32_t s = static_cast<uint32_t>(P.prompt[b + idx]);
-      const uint32_t o = static_cast<uint32_t>(P.output[b + idx]);
-      P.rec[b + r] = make_uint2(key, s | (o << 16));
-      P.rank_of[b + idx] = r;
-      if (algo == SCHED_AELL) P.u_of_rank[b + r] = P.upper[b + idx];
-    }
-  }
-}
 
 // ---------------------------------------------------------------------------
 // k_simulate
@@ -684,6 +363,7 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
     const g_u64* rec = base((const g_u64*)(P.rec + b));  // (key, s | o << 16) as one 64-bit word
     const g_i32* arrival = P.arrival ? base((const g_i32*)(P.arrival + b)) : nullptr;
     const g_i32* rank_of = base((const g_i32*)(P.rank_of + b));
+    const bool late = late_arrivals(P, b, n);
     const g_i32* upper_k = ALGO == SCHED_AELL ? (const g_i32*)(P.u_of_rank + b) : nullptr;  // by rank
     // per-request outputs by id (with tie keys: the staging arrays)
     // completion steps by id: staged in LDS after the cancelled set when the
@@ -768,7 +448,7 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
     aw_rank = 0;                                                                     \
     if (i_ < n) {                                                                    \
       aw_a = arrival ? arrival[i_] : 0;                                              \
-      aw_rank = rank_of[i_];                                                         \
+      aw_rank = late ? rank_of[i_] : i_;                                             \
     }                                                                                \
   } while (0)
     // the record of fresh rank f_rank from the 64-record window (reloaded when

@@ -86,15 +86,25 @@ struct WaveStateT {
 using WaveState = WaveStateT<10>;
 using WaveStateWide = WaveStateT<16>;
 
+// The fresh set's bitmaps at the start: empty, or where every request arrives at
+// step 0, full.  Returns the requests that need not arrive any more.
+__device__ __forceinline__ int start_waiting(const Params& P, const int64_t b, const int n, uint64_t* L0, uint64_t* L1) {
+  const int nw = (n + 63) >> 6, nw1 = (nw + 63) >> 6;
+  const uint64_t all = n > 0 && !late_arrivals(P, b, n) ? ~0ull : 0ull;
+  for (int w = threadIdx.x; w < nw; w += 64) L0[w] = w == nw - 1 ? all >> (63 - ((n - 1) & 63)) : all;
+  for (int w = threadIdx.x; w < nw1; w += 64) L1[w] = w == nw1 - 1 ? all >> (63 - ((nw - 1) & 63)) : all;
+  return all != 0ull ? n : 0;
+}
+
 // The state of an instance at step 0 (what a body starting fresh holds).
 template <typename ST>
-__device__ __forceinline__ void fresh_state(ST& st) {
+__device__ __forceinline__ void fresh_state(ST& st, const int arr_ptr) {
 #pragma unroll
   for (int r = 0; r < ST::kRows; ++r) {
     st.r_end[r] = kEmpty; st.r_x[r] = 0; st.r_c[r] = kNever; st.r_f[r] = 0; st.r_key[r] = 0xFFFFFFFFu; st.r_u[r] = 0;
   }
   st.fr_row = 0; st.fr_mask = ~0ull; st.N = 0; st.X = 0; st.t_r = 0; st.next_c = kNever;
-  st.aw_base = -64; st.aw_a = kNever; st.aw_rank = 0; st.arr_ptr = 0; st.next_a = 0;
+  st.aw_base = -64; st.aw_a = kNever; st.aw_rank = 0; st.arr_ptr = arr_ptr; st.next_a = 0;
   st.f_base = -1; st.fw_u = 0; st.fw_key = 0xFFFFFFFFu; st.fw_so = 0; st.f_word = 0ull;
   st.vw_key = threadIdx.x < 32 ? 0u : 0xFFFFFFFFu; st.vw_so = 0; st.pn_key = 0xFFFFFFFFu; st.pn_so = 0;
   st.v_lo = 32; st.v_hi = 32; st.v_sp = 0; st.n_pend = 0; st.n_ovf = 0;
@@ -168,9 +178,9 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
     const bool stage_c = P.stage_comp != 0;
     const int nw = (n + 63) >> 6;
     const int nw1 = (nw + 63) >> 6;
+    int arr_ptr = 0;  // the next request to arrive
     if (!FROM_STATE) {
-      for (int w = lane; w < nw; w += 64) L0[w] = 0;
-      for (int w = lane; w < nw1; w += 64) L1[w] = 0;
+      arr_ptr = start_waiting(P, b, n, L0, L1);
       if (stage_c)
         for (int i = lane; i < n; i += 64) lcomp[i] = -1;
       __syncthreads();
@@ -222,7 +232,7 @@ __device__ __forceinline__ int wave_instance(const Params& P, const int k, const
     int32_t X = 0;                // sum of x over runs
     int32_t t_r = 0;              // base step of x
     int32_t next_c = kNever;      // lower bound on the next completion (A_l: or promotion)
-    int32_t aw_base = -64, aw_a = kNever, aw_rank = 0, arr_ptr = 0;
+    int32_t aw_base = -64, aw_a = kNever, aw_rank = 0;
     int32_t next_a = 0;           // arrival step of request arr_ptr (0: look at step 0)
     // F: the waiting ranks of [f_base, f_base + 64) (none: no fresh request
     // waits) and their records; the LDS copy of the word may hold taken bits
@@ -1299,15 +1309,14 @@ __device__ __forceinline__ void ladder_instance(const Params& P, const int k) {
       st0 = SCHED_OK;
     }
   }
+  int arr_ptr = 0;
   if (st0 == SCHED_OK) {
     // the bodies all resume from a state, so the bitmaps and staged outputs
     // are set up here
     extern __shared__ uint64_t lds64[];
     const int64_t b = P.offsets[k];
     const int n = static_cast<int>(P.offsets[k + 1] - b);
-    const int nw = (n + 63) >> 6, nw1 = (nw + 63) >> 6;
-    for (int w = threadIdx.x; w < nw; w += 64) lds64[w] = 0;
-    for (int w = threadIdx.x; w < nw1; w += 64) lds64[P.nw_max + w] = 0;
+    arr_ptr = start_waiting(P, b, n, lds64, lds64 + P.nw_max);
     int32_t* lc = reinterpret_cast<int32_t*>(lds64 + P.nw_max + P.nw1_max + P.cap_v);
     if (P.stage_comp)
       for (int i = threadIdx.x; i < n; i += 64) lc[i] = -1;
@@ -1328,7 +1337,7 @@ __device__ __forceinline__ void ladder_instance(const Params& P, const int k) {
   }
   using ST = typename std::conditional<WIDE, WaveStateWide, WaveState>::type;
   ST st;
-  fresh_state(st);
+  fresh_state(st, arr_ptr);
   int r;
   if constexpr (!WIDE) {
     do {
@@ -1366,15 +1375,14 @@ __device__ __forceinline__ void ladder_instance(const Params& P, const int k) {
   const int k = (ORDERED_) ? P.order[blockIdx.x] : static_cast<int>(blockIdx.x);                                                       \
   if (P.algo_of && P.algo_of[k] != ALGO) return;                                                                                       \
   const int st0 = P.status[k];                                                                                                         \
+  int arr_ptr = 0;                                                                                                                 \
   if (st0 == SCHED_OK) {                                                                                                               \
     /* the bodies all resume from a state, so the bitmaps and staged outputs */                                                        \
     /* are set up here */                                                                                                              \
     extern __shared__ uint64_t lds64[];                                                                                                \
     const int64_t b = P.offsets[k];                                                                                                    \
     const int n = static_cast<int>(P.offsets[k + 1] - b);                                                                              \
-    const int nw = (n + 63) >> 6, nw1 = (nw + 63) >> 6;                                                                                \
-    for (int w = threadIdx.x; w < nw; w += 64) lds64[w] = 0;                                                                           \
-    for (int w = threadIdx.x; w < nw1; w += 64) lds64[P.nw_max + w] = 0;                                                               \
+    arr_ptr = start_waiting(P, b, n, lds64, lds64 + P.nw_max);                                                                          \
     int32_t* lc = reinterpret_cast<int32_t*>(lds64 + P.nw_max + P.nw1_max + P.cap_v);                                                  \
     if (P.stage_comp)                                                                                                                  \
       for (int i = threadIdx.x; i < n; i += 64) lc[i] = -1;                                                                            \
@@ -1394,7 +1402,7 @@ __device__ __forceinline__ void ladder_instance(const Params& P, const int k) {
     return;                                                                                                                            \
   }                                                                                                                                    \
   WaveState st;                                                                                                                         \
-  fresh_state(st);                                                                                                                     \
+  fresh_state(st, arr_ptr);                                                                                                                  \
   int r;                                                                                                                               \
   do {                                                                                                                                 \
     switch (st.next_rows) {                                                                                                            \
