@@ -1,30 +1,19 @@
 // sim_device.hpp -- gfx950 kernels of the scheduler simulator (device code).
 //
-// One wave64 simulates one instance from t = 0 to its last completion (or a
-// workgroup of W waves, see group_exchange); nothing returns to the host
-// between steps.
+// What every kernel shares (the parameters and limits of a launch), and the
+// simulation of one instance by a workgroup of W waves (k_simulate_group, see
+// group_exchange) for running sets beyond one wave's 1024 runs.  An instance that a
+// single wave holds is simulated by the code of sim_wave.hpp, a batch of tiny ones by
+// that of sim_tiny.hpp; prepare.hpp checks and ranks the requests beforehand.
 //
-// k_prepare (per instance): validates the requests, computes the default step
-//   cap, initialises the per-request outputs, and ranks the requests by
-//   (initial planning length, tie key, index) with a stable LSD radix sort
-//   (8-bit digits, LDS histogram, ballot-based stable scatter).  The ranked
-//   records (key, s | o << 16) go to a workspace slice of the instance.
-//
-// k_simulate_ladder / k_simulate_ladder_wide / k_simulate / k_simulate_group
-// (per instance), one body per policy (A_max, A_min, H-SF, A_l, A_random; the
-// adaptive policy runs the A_min and the A_l bodies, each on its own
-// instances), state:
-//   running set R    -- ROWS x 64 register slots, row r lane j holds one run:
+// State of a workgroup's simulation:
+//   running set R    -- ROWS x 64 register slots a wave, row r lane j holds one run:
 //                       planned end Rend = p + est, x = s - p + t_r, completion
 //                       C = p + o, key = est << 17 | rank, and h = f(Rend) +
 //                       Rend - t_r, where f(c) is the planned memory at step c of
 //                       all runs whose planned end is >= c (equation (2) summed
 //                       over the planned set).  t_r is a base step that keeps the
-//                       int32 values small (rebased every 2^16 steps).  A wave
-//                       moves, state and all, along a ladder of bodies with 2, 3,
-//                       5, 8, 10 (then 12, 16) rows as its running set grows and
-//                       shrinks; instances beyond 1024 runs go to workgroups.
-//                       Scans cover every row of the current body.
+//                       int32 values small (rebased every 2^16 steps).
 //   fresh waiting F  -- two-level bitmap over key ranks in LDS; the smallest
 //                       waiting key is the first set bit.  Its word is cached in
 //                       scalar registers until it empties.
@@ -170,40 +159,6 @@ __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) {
   return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int32_t>(v)));
 }
 
-// The loop-carried state of one instance's simulation, handed from one body
-// to another with a different number of register rows (the row ladder: 2, 3,
-// 5, 8, 10 rows).  A body grows at an admission that finds no free slot (the
-// next body's extra rows start empty) and shrinks, at the start of a step's
-// admissions, once the running set fits a smaller body with room to spare (it
-// first moves the runs of its upper rows into free slots of the lower ones).
-// The LDS sets stay where they are.  `resume`: continue with the admissions of
-// step t (false: start step t from its arrivals).
-template <int SR>
-struct SimStateT {
-  static constexpr int kRows = SR;
-  int32_t r_end[SR], r_x[SR], r_c[SR], r_h[SR], r_u[SR];
-  uint32_t r_key[SR];
-  int fr_row;
-  uint64_t fr_mask;
-  int32_t N, X, t_r, next_c, aw_base, aw_a, aw_rank, arr_ptr, next_a, f_rank, fw_base, f_u, fw_u;
-  uint32_t f_key, f_so, fw_key, fw_so, v_key, v_so;
-  uint64_t f_word;
-  int32_t nV, nVe, v_pos, v_head, v_u, n_done, retry_at, t, DT;
-  int64_t rsteps, tot_ev;
-  uint32_t u_key, u_so, u_gate;   // A_min: the register row of recent cancellations (per lane)
-  uint64_t u_used;
-  uint32_t uh_key, uh_so;
-  int32_t uh_lane;
-  int32_t next_rows;
-  bool resume;
-  uint32_t vw_lo, vw_hi;          // A_l: register window of the promoted queue (per lane)
-  int32_t vw_base;
-};
-// the narrow ladder (up to 10 rows, four waves a SIMD) and the wide one (up
-// to 16 rows, for few large instances and for instances that outgrow the
-// narrow one)
-using SimState = SimStateT<10>;
-using SimStateWide = SimStateT<16>;
 // Status of a body that handed its state over (TO_STATE) instead of ending.
 constexpr int kResume = -102;
 
@@ -278,56 +233,46 @@ __device__ __forceinline__ int32_t lanes_sum_i32(int32_t v) {
   return wave::uniform(static_cast<int32_t>(wave::fold_in_row(static_cast<uint32_t>(v), wave::OpAddU32{})));
 }
 
-// Simulates instance k (whose validation status is st0) with ROWS register
-// rows and writes its outputs.  A running set that outgrows the rows ends the
-// simulation with `retry_status` (the per-request outputs are then reset), or,
-// with TO_STATE, saves the state to *st and returns kResume at once.  With
-// FROM_STATE the body continues from *st instead of starting at step 0.  A
-// cancelled set that outgrows its P.cap_v LDS slots ends it with
-// P.retry_v_status; with VGLOBAL the set lives in global memory (n slots, the
-// most it can hold).  CAPPED holds the running set to P.run_cap runs.  W > 1:
-// a workgroup of W waves simulates the instance (see group_exchange).
-template <int ALGO, int ROWS, bool FROM_STATE = false, bool TO_STATE = false, bool VGLOBAL = false,
-          bool CAPPED = false, typename ST = SimState, int W = 1, bool CLS = true, bool PRIO = true>
-__device__ __forceinline__ int sim_instance(const Params& P, const int k, const int st0, const int retry_status,
-                                           ST* st = nullptr) {
-  constexpr int kStateRows = ST::kRows;
-  static_assert(!(FROM_STATE || TO_STATE) || ROWS <= kStateRows, "state holds at most kStateRows rows");
-  static_assert(W == 1 || (W <= 16 && !FROM_STATE && !TO_STATE && !CAPPED), "a workgroup runs fixed rows");
+// Simulates instance k (whose validation status is st0) on a workgroup of W
+// waves with ROWS register rows each (see group_exchange) and writes its outputs.  A
+// running set that outgrows the rows ends the simulation with `retry_status` (the
+// per-request outputs are then reset).  A cancelled set that outgrows its P.cap_v LDS
+// slots ends it with P.retry_v_status; with VGLOBAL the set lives in global memory (n
+// slots a wave, the most it can hold).
+template <int ALGO, int ROWS, bool VGLOBAL, int W>
+__device__ __forceinline__ void sim_instance(const Params& P, const int k, const int st0, const int retry_status) {
+  static_assert(W > 1 && W <= 16, "one wave alone is wave_instance's");
   // only A_min and A_l have cancelled (or promoted) requests waiting: for the
   // other policies every head is fresh, and the code of the cancelled set is
   // left out of their kernels
   constexpr bool kHasV = ALGO == SCHED_AMIN || ALGO == SCHED_AELL;
   extern __shared__ uint64_t lds64[];
-  const int lane = W > 1 ? static_cast<int>(threadIdx.x & 63u) : static_cast<int>(threadIdx.x);
-  const int wv = W > 1 ? wave::uniform(static_cast<int32_t>(threadIdx.x >> 6)) : 0;
+  const int lane = static_cast<int>(threadIdx.x & 63u);
+  const int wv = wave::uniform(static_cast<int32_t>(threadIdx.x >> 6));
   const int64_t b = P.offsets[k];
-  // a body that hands its state over only ever runs valid, non-empty instances
-  const int n = (TO_STATE || st0 == SCHED_OK) ? static_cast<int>(P.offsets[k + 1] - b) : 0;
+  const int n = st0 == SCHED_OK ? static_cast<int>(P.offsets[k + 1] - b) : 0;
   const int32_t M = P.M;
 
   int status = st0;
-  int handoff = 0;  // TO_STATE: rows of the body that continues (status kResume)
   // counters live in vector registers (see wave::in_vgpr)
-  int64_t rsteps = wave::in_vgpr<int64_t>(FROM_STATE ? st->rsteps : 0);
-  int64_t tot_ev = wave::in_vgpr<int64_t>(FROM_STATE ? st->tot_ev : 0);
+  int64_t rsteps = wave::in_vgpr<int64_t>(0);
+  int64_t tot_ev = wave::in_vgpr<int64_t>(0);
 
-  if (TO_STATE || (st0 == SCHED_OK && n > 0)) {
-    // W > 1: each wave's block (bitmaps, cancelled set) follows the exchange
+  if (st0 == SCHED_OK && n > 0) {
+    // each wave's block (bitmaps, cancelled set) follows the exchange
     // area, and the staged completion steps (one array for the workgroup)
     // follow the blocks; a global cancelled set has n entries per wave
     const int gstride = P.nw_max + P.nw1_max + (VGLOBAL ? 0 : P.cap_v);
-    uint64_t* const lw = W > 1 ? lds64 + group_pre_words(ALGO, W, ROWS) + wv * gstride : lds64;
+    uint64_t* const lw = lds64 + group_pre_words(ALGO, W, ROWS) + wv * gstride;
     uint64_t* L0 = lw;
     uint64_t* L1 = lw + P.nw_max;
     // cancelled requests, one 64-bit entry each.  A_min: key | (s | o << 16) << 32,
     // slots [0, nVe) may start now, [nVe, nV) were cancelled at this step.
     // A_l: a FIFO ring of id | s << 17 | o << 33 | u << 48 from slot v_head.
-    // (W > 1, global: each wave of workgroup g has the n_max entries at
+    // (global: each wave of workgroup g has the n_max entries at
     // P.vgroup + (g W + wave) n_max; the workgroup simulates its instances
     // one after the other)
-    uint64_t* vent = VGLOBAL ? (W > 1 ? P.vgroup + (static_cast<int64_t>(blockIdx.x) * W + wv) * P.max_requests
-                                      : P.vglob + b)
+    uint64_t* vent = VGLOBAL ? P.vgroup + (static_cast<int64_t>(blockIdx.x) * W + wv) * P.max_requests
                              : L1 + P.nw1_max;
     // A_l: every request is promoted at most once, so its queue is an
     // append-only array of n entries in global memory (the instance's slice
@@ -335,19 +280,16 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
     constexpr bool kQueue = ALGO == SCHED_AELL;
     g_u64* qg = kQueue ? (g_u64*)(P.vglob + b) : nullptr;
     const int32_t cap_v = (VGLOBAL || kQueue) ? n : P.cap_v;
-    int32_t* lcomp = W > 1 ? reinterpret_cast<int32_t*>(lds64 + group_pre_words(ALGO, W, ROWS) + W * gstride)
-                           : reinterpret_cast<int32_t*>(L1 + P.nw1_max + (VGLOBAL ? 0 : P.cap_v));
+    int32_t* lcomp = reinterpret_cast<int32_t*>(lds64 + group_pre_words(ALGO, W, ROWS) + W * gstride);
     const bool stage_c = P.stage_comp != 0;
     const int nw = (n + 63) >> 6;
     const int nw1 = (nw + 63) >> 6;
-    if (!FROM_STATE) {
-      for (int w = lane; w < nw; w += 64) L0[w] = 0;
-      for (int w = lane; w < nw1; w += 64) L1[w] = 0;
-      if (stage_c)
-        for (int i = W > 1 ? static_cast<int>(threadIdx.x) : lane; i < n; i += 64 * W) lcomp[i] = -1;
-      __syncthreads();
-    }
-    // W > 1: the exchange buffers, the completion lists, the run counts
+    for (int w = lane; w < nw; w += 64) L0[w] = 0;
+    for (int w = lane; w < nw1; w += 64) L1[w] = 0;
+    if (stage_c)
+      for (int i = static_cast<int>(threadIdx.x); i < n; i += 64 * W) lcomp[i] = -1;
+    __syncthreads();
+    // the exchange buffers, the completion lists, the run counts
     uint4* const gred = reinterpret_cast<uint4*>(lds64);
     uint64_t* const glist = lds64 + 8 * W + wv * 64 * ROWS;
     int gpar = 0;
@@ -371,7 +313,7 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
     // instance), else straight to the global outputs.  One generic pointer,
     // so the staged case costs no registers (its stores are flat stores to
     // LDS; the global case's are flat stores too, which measured the same)
-    int32_t* cdst = base(P.stage_comp ? (W > 1 ? lcomp : reinterpret_cast<int32_t*>(lds64 + P.nw_max + P.nw1_max + (VGLOBAL ? 0 : P.cap_v)))
+    int32_t* cdst = base(P.stage_comp ? lcomp
                                       : (P.tie_key ? P.comp_st : P.completion) + b);
     g_i32* evictions = P.evictions ? base((g_i32*)((P.tie_key ? P.ev_st : P.evictions) + b)) : nullptr;
 
@@ -383,10 +325,6 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
       r_end[r] = kEmpty; r_x[r] = 0; r_c[r] = kNever; r_h[r] = 0; r_key[r] = 0xFFFFFFFFu; r_u[r] = 0;
-      if (FROM_STATE) {
-        r_end[r] = st->r_end[r]; r_x[r] = st->r_x[r]; r_c[r] = st->r_c[r];
-        r_h[r] = st->r_h[r]; r_key[r] = st->r_key[r]; r_u[r] = st->r_u[r];
-      }
     }
     int fr_row = 0;               // row that receives new runs ...
     uint64_t fr_mask = ~0ull;     // ... and its free lanes
@@ -424,21 +362,6 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
     int32_t retry_at = 0;
     int32_t t = 0;
     int32_t DT = 0;               // memory held at t by the runs completing at t
-    if (FROM_STATE) {
-      fr_row = st->fr_row; fr_mask = st->fr_mask; N = st->N; X = st->X; t_r = st->t_r; next_c = st->next_c;
-      aw_base = st->aw_base; aw_a = st->aw_a; aw_rank = st->aw_rank; arr_ptr = st->arr_ptr; next_a = st->next_a;
-      f_rank = st->f_rank; f_word = st->f_word; fw_base = st->fw_base; f_key = st->f_key; f_so = st->f_so; fw_key = st->fw_key;
-      fw_so = st->fw_so; f_u = st->f_u; fw_u = st->fw_u;
-      nV = st->nV; nVe = st->nVe; v_pos = st->v_pos; v_head = st->v_head; v_key = st->v_key; v_so = st->v_so;
-      v_u = st->v_u; n_done = st->n_done; retry_at = st->retry_at; t = st->t; DT = st->DT;
-      if constexpr (ALGO == SCHED_AMIN) {
-        u_key = st->u_key; u_so = st->u_so; u_gate = st->u_gate; u_used = st->u_used;
-        uh_key = st->uh_key; uh_so = st->uh_so; uh_lane = st->uh_lane;
-      }
-      if constexpr (ALGO == SCHED_AELL) {
-        vw_lo = st->vw_lo; vw_hi = st->vw_hi; vw_base = st->vw_base;
-      }
-    }
 
 #define SK_LOAD_ARRIVALS()                                                           \
   do {                                                                               \
@@ -646,14 +569,11 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
     // fraction), so the instances that bound the launch are not slowed by
     // their SIMD-mates; where a batch mixes interval widths (A_min with upper
     // bounds), the static class of the instance and whether half of it is
-    // done instead (PRIO false: none).  Outputs do not depend on it.
+    // done instead.  Outputs do not depend on it.
     int prio = -1;
-    // (CLS false: an instance of the code without the class read, for the
-    // launches that never have classes)
-    const int pcls = CLS ? ((ALGO == SCHED_AMIN && P.pclass) ? P.pclass[k] : -1) : -1;
+    const int pcls = (ALGO == SCHED_AMIN && P.pclass) ? P.pclass[k] : -1;
 #define SK_SET_PRIORITY()                                                            \
   do {                                                                               \
-    if (!PRIO) break;                                                                \
     const int lv_ = pcls >= 0 ? pcls + (2 * (n - n_done) > n ? 1 : 0) : (4 * (n - n_done) - 1) / n; \
     if (lv_ != prio) {                                                               \
       prio = lv_;                                                                    \
@@ -664,37 +584,7 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
     }                                                                                \
   } while (0)
     SK_SET_PRIORITY();
-    // the state at the admissions of step t, for the body with NR_ rows
-#define SK_SAVE_STATE(NR_)                                                             \
-  do {                                                                                 \
-    _Pragma("unroll") for (int r = 0; r < kStateRows; ++r) {                           \
-      const bool have = r < ROWS;                                                      \
-      st->r_end[r] = have ? r_end[r < ROWS ? r : 0] : kEmpty;                          \
-      st->r_x[r] = have ? r_x[r < ROWS ? r : 0] : 0;                                   \
-      st->r_c[r] = have ? r_c[r < ROWS ? r : 0] : kNever;                              \
-      st->r_h[r] = have ? r_h[r < ROWS ? r : 0] : 0;                                   \
-      st->r_key[r] = have ? r_key[r < ROWS ? r : 0] : 0xFFFFFFFFu;                     \
-      st->r_u[r] = have ? r_u[r < ROWS ? r : 0] : 0;                                   \
-    }                                                                                  \
-    st->fr_row = fr_row; st->fr_mask = fr_mask; st->N = N; st->X = X; st->t_r = t_r;   \
-    st->next_c = next_c; st->aw_base = aw_base; st->aw_a = aw_a; st->aw_rank = aw_rank; \
-    st->arr_ptr = arr_ptr; st->next_a = next_a; st->f_rank = f_rank; st->f_word = f_word; \
-    st->fw_base = fw_base; st->f_key = f_key; st->f_so = f_so; st->fw_key = fw_key;    \
-    st->fw_so = fw_so; st->f_u = f_u; st->fw_u = fw_u; st->nV = nV; st->nVe = nVe;     \
-    st->v_pos = v_pos; st->v_head = v_head; st->v_key = v_key; st->v_so = v_so;        \
-    st->v_u = v_u; st->n_done = n_done; st->retry_at = retry_at; st->t = t; st->DT = DT; \
-    st->rsteps = rsteps; st->tot_ev = tot_ev; st->next_rows = (NR_); st->resume = true; \
-    if constexpr (ALGO == SCHED_AMIN) {                                                \
-      st->u_key = u_key; st->u_so = u_so; st->u_gate = u_gate; st->u_used = u_used;   \
-      st->uh_key = uh_key; st->uh_so = uh_so; st->uh_lane = uh_lane;                  \
-    }                                                                                  \
-    if constexpr (ALGO == SCHED_AELL) {                                                \
-      st->vw_lo = vw_lo; st->vw_hi = vw_hi; st->vw_base = vw_base;                     \
-    }                                                                                  \
-  } while (0)
-    bool resuming = FROM_STATE && st->resume;   // continue with the admissions of step t
     for (;;) {
-      if (!resuming) {
       if (t > cap) {
         status = SCHED_E_STEP_CAP;
         break;
@@ -786,15 +676,15 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
       if (t >= next_c) {
         int32_t sx = 0;
         int ndone = 0;
-        int lc = 0;                    // W > 1: this wave's completions listed
-        uint32_t gcmin = 0xFFFFFFFFu;  // W > 1: the next event, agreed
+        int lc = 0;                    // this wave's completions listed
+        uint32_t gcmin = 0xFFFFFFFFu;  // the next event, agreed
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
           const bool hit = r_c[r] == t;
           const uint64_t m = wave::ballot(hit);
           if (m) {
             ndone += __builtin_popcountll(m);
-            if constexpr (W > 1 && (ALGO == SCHED_AMAX || ALGO == SCHED_AELL)) {
+            if constexpr (ALGO == SCHED_AMAX || ALGO == SCHED_AELL) {
               // every wave drops the shares of every wave's completions: list them
               if (hit) {
                 const int pos = lc + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
@@ -821,7 +711,7 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
             if (r == fr_row) fr_mask |= m;
           }
         }
-        if constexpr (W > 1) {
+        {
           // agree on the completions (and, but for A_l, the next one)
           uint32_t cl = 0xFFFFFFFFu;
           if constexpr (ALGO != SCHED_AELL) {
@@ -866,14 +756,6 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
             n_done += nd;
             SK_SET_PRIORITY();
           }
-        } else if (ndone) {
-          event = true;
-          const int32_t sxw = wave::sum_i32(sx);
-          X -= sxw;
-          N -= ndone;
-          DT = sxw + ndone * (t - t_r);
-          n_done += ndone;
-          SK_SET_PRIORITY();
         }
         // ---- 3. done?
         if (n_done == n) break;
@@ -882,7 +764,7 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
         // the queue, lowest index first among this step's promotions
         if (ALGO == SCHED_AELL) {
           bool promoted = false;
-          if constexpr (W > 1) {
+          {
           for (;;) {
             uint32_t best = 0xFFFFFFFFu;
             int32_t brow = 0;
@@ -964,57 +846,6 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
             ++tot_ev;
             promoted = true;
           }
-          } else {
-          for (;;) {
-            uint32_t best = 0xFFFFFFFFu;
-            int32_t brow = 0;
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) {
-              const uint32_t kk = r_end[r] == t ? (r_key[r] & kIdxMask) : 0xFFFFFFFFu;
-              const bool lt = kk < best;
-              best = lt ? kk : best;
-              brow = lt ? r : brow;
-            }
-            const uint32_t iv = wave::min_u32_all(best);
-            const uint64_t at = wave::ballot(best == iv);
-            const uint32_t imin = wave::uniform_u(iv);
-            if (imin == 0xFFFFFFFFu) break;
-            if (nV >= cap_v) {
-              status = P.retry_v_status;
-              break;
-            }
-            const int ln = __builtin_ctzll(at);
-            const int rr = wave::readlane(brow, ln);
-            int32_t xk = 0, ck = 0, uk = 0;
-            uint32_t kk = 0;
-            SK_AT_ROW(rr, xk = wave::readlane(r_x[r], ln); ck = wave::readlane(r_c[r], ln);
-                      uk = wave::readlane(r_u[r], ln); kk = wave::readlane_u(r_key[r], ln);
-                      r_end[r] = wave::writelane(r_end[r], kEmpty, ln);
-                      r_c[r] = wave::writelane(r_c[r], kNever, ln);
-                      r_key[r] = wave::writelane_u(r_key[r], 0xFFFFFFFFu, ln);)
-            if (rr == fr_row) fr_mask |= 1ull << ln;
-            // its planned end is t itself: no later planned end loses a share
-            X -= xk;
-            N -= 1;
-            const int32_t pk = t - static_cast<int32_t>(kk >> kIdxBits);
-            const uint64_t sk = static_cast<uint32_t>(xk - t_r + pk);
-            const uint64_t okk = static_cast<uint32_t>(ck - pk);
-            {
-              const int slot = v_head + nV;  // < n: each request is promoted at most once
-              const uint64_t qe = imin | (sk << 17) | (okk << 33) | (static_cast<uint64_t>(uk) << 48);
-              if (lane == 0) {
-                qg[slot] = qe;
-                if (evictions) __hip_atomic_fetch_add(&evictions[imin], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              }
-              if (slot >= vw_base && slot - vw_base < 64) {
-                vw_lo = wave::writelane_u(vw_lo, static_cast<uint32_t>(qe), slot - vw_base);
-                vw_hi = wave::writelane_u(vw_hi, static_cast<uint32_t>(qe >> 32), slot - vw_base);
-              }
-            }
-            ++nV;
-            ++tot_ev;
-            promoted = true;
-          }
           }
           if (status != SCHED_OK) break;
           if (promoted) {
@@ -1024,21 +855,7 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
         }
         // next event: a completion (A_l: or a planned end, where a run is promoted);
         // empty slots read as unsigned are above every step
-        if constexpr (W > 1) {
-          next_c = static_cast<int32_t>(gcmin);
-        } else {
-        uint32_t cmin = 0xFFFFFFFFu;
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-          uint32_t ev = static_cast<uint32_t>(r_c[r]);
-          if (ALGO == SCHED_AELL) {
-            const uint32_t pe = static_cast<uint32_t>(r_end[r]);
-            ev = pe < ev ? pe : ev;
-          }
-          cmin = ev < cmin ? ev : cmin;
-        }
-        next_c = static_cast<int32_t>(wave::min_u32(cmin));  // kNever when nothing runs
-        }
+        next_c = static_cast<int32_t>(gcmin);
       }
 
       // ---- 4. A_min: cancel in ascending (o~, index) while memory at t+1 > M
@@ -1058,7 +875,7 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
             const uint64_t at = wave::ballot(best == kv);
             uint32_t kmin = 0xFFFFFFFFu;
             int32_t ek = 0, xk = 0, ck = 0;
-            if constexpr (W > 1) {
+            {
               // the smallest key over the waves; its wave removes the run
               const uint32_t kl = wave::uniform_u(kv);
               int ln = 0, rr = 0;
@@ -1092,23 +909,6 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
                 if (rr == fr_row) fr_mask |= 1ull << ln;
               }
               occ -= lane == win ? 1 : 0;
-            } else {
-            kmin = wave::uniform_u(kv);
-            if (kmin == 0xFFFFFFFFu) {  // no run: impossible while P > M > 0
-              status = SCHED_E_UNSUPPORTED;
-              break;
-            }
-            if (u_used == ~0ull && nV >= cap_v) {
-              status = P.retry_v_status;
-              break;
-            }
-            const int ln = __builtin_ctzll(at);
-            const int rr = wave::readlane(brow, ln);
-            SK_AT_ROW(rr, ek = wave::readlane(r_end[r], ln); xk = wave::readlane(r_x[r], ln);
-                      ck = wave::readlane(r_c[r], ln); r_end[r] = wave::writelane(r_end[r], kEmpty, ln);
-                      r_c[r] = wave::writelane(r_c[r], kNever, ln);
-                      r_key[r] = wave::writelane_u(r_key[r], 0xFFFFFFFFu, ln);)
-            if (rr == fr_row) fr_mask |= 1ull << ln;
             }
             SK_DROP_SHARE(t, xk, ek);
             X -= xk;
@@ -1147,61 +947,6 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
         }
       }
       if (event) retry_at = 0;
-      }
-      resuming = false;
-
-      // ---- shrink: once the runs fit a smaller body with room to spare, move
-      // the runs of the upper rows into free slots of the lower ones (the
-      // order of slots never matters: every choice is by key) and hand over
-      if constexpr (TO_STATE && ROWS > 2) {
-        int target = 0;
-        if (N <= 64 * 2 - kShrinkSpare) target = 2;
-        else if (ROWS > 3 && N <= 64 * 3 - kShrinkSpare) target = 3;
-        else if (ROWS > 5 && N <= 64 * 5 - kShrinkSpare) target = 5;
-        else if (ROWS > 8 && N <= 64 * 8 - kShrinkSpare) target = 8;
-        else if (ROWS > 10 && N <= 64 * 10 - kShrinkSpare) target = 10;
-        else if (ROWS > 12 && N <= 64 * 12 - kShrinkSpare) target = 12;
-        if (target > 0) {
-          uint64_t fm[ROWS];
-#pragma unroll
-          for (int r = 0; r < ROWS; ++r) fm[r] = wave::ballot(r_end[r] == kEmpty);
-#pragma unroll
-          for (int h = ROWS - 1; h >= 2; --h) {
-            if (h < target) break;
-            uint64_t m = ~fm[h];
-            while (m) {
-              const int ln = __builtin_ctzll(m);
-              m &= m - 1;
-              // the lowest row below the target with a free lane
-              int l = 0;
-              uint64_t fl_mask = 0;
-#pragma unroll
-              for (int r = ROWS - 1; r >= 0; --r) {
-                const bool ok = r < target && fm[r] != 0ull;
-                l = ok ? r : l;
-                fl_mask = ok ? fm[r] : fl_mask;
-              }
-              const int fl = __builtin_ctzll(fl_mask);
-              const int32_t me = wave::readlane(r_end[h], ln), mx = wave::readlane(r_x[h], ln);
-              const int32_t mc = wave::readlane(r_c[h], ln), mh = wave::readlane(r_h[h], ln);
-              const int32_t mu = wave::readlane(r_u[h], ln);
-              const uint32_t mk = wave::readlane_u(r_key[h], ln);
-              SK_AT_ROW(l, r_end[r] = wave::writelane(r_end[r], me, fl); r_x[r] = wave::writelane(r_x[r], mx, fl);
-                        r_c[r] = wave::writelane(r_c[r], mc, fl); r_h[r] = wave::writelane(r_h[r], mh, fl);
-                        r_u[r] = wave::writelane(r_u[r], mu, fl); r_key[r] = wave::writelane_u(r_key[r], mk, fl);
-                        fm[r] &= ~(1ull << fl);)
-              r_end[h] = wave::writelane(r_end[h], kEmpty, ln);
-              r_c[h] = wave::writelane(r_c[h], kNever, ln);
-              r_key[h] = wave::writelane_u(r_key[h], 0xFFFFFFFFu, ln);
-            }
-          }
-          fr_row = 0;
-          fr_mask = 0ull;  // the next admission looks for a free row
-          handoff = target;
-          status = kResume;
-          break;
-        }
-      }
 
       // ---- 5. admission of the longest feasible prefix in key order
       bool stuck = true;          // the head cannot start before the next event
@@ -1239,7 +984,7 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
           hmx = hv > hmx ? hv : hmx;
           fl += e >= E ? r_x[r] + cE : 0;
         }
-        if constexpr (W > 1) {
+        {
           // one exchange agrees on both conditions and on the step to retry at
           // (both ways of failing are prepared, see below)
           int32_t fix = 0, emin = kNever;
@@ -1302,12 +1047,8 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
         const int32_t f = wave::uniform(fv);
         // admit: start at p = t; runs whose planned end is in (t+1, E] gain its share
         // a free slot first: without one nothing has changed for this candidate
-        if (CAPPED && N >= P.run_cap) {
-          status = retry_status;
-          break;
-        }
-        int owner = 0;  // W > 1: the wave that takes the run
-        if constexpr (W > 1) {
+        int owner = 0;  // the wave that takes the run
+        {
           // the wave with the fewest runs (the lowest such); all full: outgrown
           const uint32_t oc = lane < W ? (static_cast<uint32_t>(occ) << 4) | static_cast<uint32_t>(lane) : 0xFFFFFFFFu;
           const uint32_t om = lanes_min_u32(oc);
@@ -1330,27 +1071,6 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
             fr_row = rr;
             fr_mask = mm;
           }
-        } else if (fr_mask == 0ull) {
-          int rr = -1;
-          uint64_t mm = 0ull;
-#pragma unroll
-          for (int r = ROWS - 1; r >= 0; --r) {
-            const uint64_t m = wave::ballot(r_end[r] == kEmpty);
-            rr = m ? r : rr;
-            mm = m ? m : mm;
-          }
-          if (rr < 0) {
-            if (TO_STATE && ladder_up(ROWS, kStateRows) > 0) {
-              // hand the state at this admission to the body above
-              handoff = ladder_up(ROWS, kStateRows);
-              status = kResume;
-            } else {
-              status = retry_status;
-            }
-            break;
-          }
-          fr_row = rr;
-          fr_mask = mm;
         }
         const int32_t xw = s - t + t_r;
         const int32_t hw = f + (xw + cE) + cE;
@@ -1364,7 +1084,7 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
         }
         {
           const int32_t cw = t + c_o;
-          if (W == 1 || wv == owner) {
+          if (wv == owner) {
           const int ln = __builtin_ctzll(fr_mask);
           fr_mask &= fr_mask - 1;
           const uint32_t kw = c_key;
@@ -1440,12 +1160,6 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
       }
       t = tn;
     }
-    // every way out of a handing-over body writes the whole state (so that the
-    // state a body started from is dead while it runs)
-    if constexpr (TO_STATE) {
-      SK_SAVE_STATE(handoff);
-      if (status == kResume) return kResume;
-    }
   }
 
   // ---- epilogue: totals from the per-request outputs (with tie keys, first
@@ -1457,11 +1171,10 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
   int64_t tel = 0, mk = 0;
   if (keep) {
     const int32_t* lc =
-        W > 1 ? reinterpret_cast<const int32_t*>(lds64 + group_pre_words(ALGO, W, ROWS) +
-                                                 W * (P.nw_max + P.nw1_max + (VGLOBAL ? 0 : P.cap_v)))
-              : reinterpret_cast<const int32_t*>(lds64 + P.nw_max + P.nw1_max + (VGLOBAL ? 0 : P.cap_v));
+        reinterpret_cast<const int32_t*>(lds64 + group_pre_words(ALGO, W, ROWS) +
+                                         W * (P.nw_max + P.nw1_max + (VGLOBAL ? 0 : P.cap_v)));
     for (int c = 0; c < n; c += 64 * W) {
-      const int i = c + (W > 1 ? static_cast<int>(threadIdx.x) : lane);
+      const int i = c + static_cast<int>(threadIdx.x);
       if (i < n) {
         const int32_t id = tie ? P.tr_of[b + i] : i;
         int32_t ci;
@@ -1484,7 +1197,7 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
     int32_t* comp = tie ? P.comp_st : P.completion;
     int32_t* evs = tie ? P.ev_st : P.evictions;
     for (int c = 0; c < n; c += 64 * W) {
-      const int i = c + (W > 1 ? static_cast<int>(threadIdx.x) : lane);
+      const int i = c + static_cast<int>(threadIdx.x);
       if (i < n) {
         comp[b + i] = -1;
         if (P.evictions) evs[b + i] = 0;
@@ -1493,7 +1206,7 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
   }
   tel = wave::sum_i64(tel);
   mk = wave::max_i64(mk);
-  if constexpr (W > 1) {
+  {
     // over the waves (the exchange area is free: every wave is past the
     // barrier above, so past its last exchange)
     int64_t* gt = reinterpret_cast<int64_t*>(lds64);
@@ -1513,14 +1226,13 @@ __device__ __forceinline__ int sim_instance(const Params& P, const int k, const 
     rsteps = 0;
     tot_ev = 0;
   }
-  if (W > 1 ? threadIdx.x == 0 : lane == 0) {
+  if (threadIdx.x == 0) {
     P.total_latency[k] = tel;
     if (P.makespan) P.makespan[k] = static_cast<int32_t>(mk);
     if (P.request_steps) P.request_steps[k] = rsteps;
     if (P.total_evictions) P.total_evictions[k] = tot_ev;
     P.status[k] = status;
   }
-  return status;
 }
 
 // A workgroup of W waves per instance, ROWS register rows each (W x 64 x ROWS
@@ -1540,12 +1252,11 @@ __global__ __launch_bounds__(64 * W) void k_simulate_group(Params P) {
       if (!take) continue;
       st0 = SCHED_OK;
     }
-    sim_instance<ALGO, ROWS, false, false, VGLOBAL, false, SimState, W>(P, k, st0, P.retry_status);
+    sim_instance<ALGO, ROWS, VGLOBAL, W>(P, k, st0, P.retry_status);
     __syncthreads();  // the next instance reuses the LDS
   }
 }
 #undef SK_SET_PRIORITY
-#undef SK_SAVE_STATE
 #undef SK_LOAD_ARRIVALS
 #undef SK_PICK
 #undef SK_F_FIND
