@@ -607,6 +607,10 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
         group_words = std::max<int64_t>(group_words, per * t.grid);
       } else {
         any_global = any_global || t.vglobal;
+        // (a retry pass has few instances to take, often none: its workgroups look
+        // through the statuses instead of being started for one each, 200 us for
+        // the 65536 of a sweep)
+        if (t.gw > 1 && t.retry) t.grid = static_cast<int>(std::min<int64_t>(in->num_instances, 16 * int64_t(n_cu)));
       }
       if (t.gw > 1 && !sim_kernel_any(sim_algos[a], t)) return SCHED_E_UNSUPPORTED;
     }
