@@ -159,7 +159,7 @@ __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) {
   return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int32_t>(v)));
 }
 
-// Status of a body that handed its state over (TO_STATE) instead of ending.
+// Status of a one-wave body that handed its state over (sim_wave.hpp) instead of ending.
 constexpr int kResume = -102;
 
 // The row ladders: the body above each rung (0: none).  The narrow ladder
@@ -176,7 +176,7 @@ constexpr int kShrinkSpare = 16;
 constexpr int kURowFlush = 48;
 
 // ---------------------------------------------------------------------------
-// A workgroup of W > 1 waves simulating one instance.  Every wave holds its
+// A workgroup of W waves simulating one instance.  Every wave holds its
 // own ROWS register rows of the running set (W x 64 x ROWS slots) and its own
 // copy of the rest of the state (the bitmaps and the cancelled set in an LDS
 // block of its own, the scalars, the register row of recent cancellations),
