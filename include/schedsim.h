@@ -239,8 +239,9 @@ int sched_validate(const sched_instances_t* instances, int32_t algo, int64_t M, 
  * true outputs and keeps equation (1) (the OPT of the competitive analysis,
  * Section 2), by exhaustive branch and bound on the GPU: a first launch gives
  * every instance one wave (its 64 lanes test 64 start steps of a request at
- * once) and at most 2^17 nodes (fewer in smaller batches; node_cap when that is
- * at most 2^17, which is then the only launch); the instances not finished by then are
+ * once) and at most 2^17 nodes (fewer in smaller batches where max a + sum(o + 1) +
+ * 1 + max o is at most 63; node_cap when that is at most 2^17, which is then the only
+ * launch); the instances not finished by then are
  * searched again by a second launch of as many 16-wave workgroups as the
  * device holds at once, whose waves claim the pieces below the starts of an
  * instance's first two requests one at a time from any unfinished instance

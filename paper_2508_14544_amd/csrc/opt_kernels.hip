@@ -62,6 +62,7 @@ struct OptParams {
   const int32_t* output;
   int32_t M;
   int64_t node_cap;
+  int64_t wide_cap;         // first launch: the budget of an instance that does not fit a memory profile
   const int64_t* upper_bound;
   int64_t* total_latency;
   int32_t* status;
@@ -497,22 +498,25 @@ __device__ __forceinline__ int setup(const OptParams& P, const int k, Inst& I, S
   return status;
 }
 
-// First launch: one wave per instance, at most P.node_cap nodes; an instance
-// not finished within them gets P.unfinished (the second launch's mark, with
-// the best total found as its bound, or SCHED_E_STEP_CAP).
+// First launch: one wave per instance, at most P.node_cap nodes (P.wide_cap where
+// it does not fit a memory profile); an instance not finished within them gets
+// P.unfinished (the second launch's mark, with the best total found as its
+// bound, or SCHED_E_STEP_CAP).
 __global__ __launch_bounds__(64) void k_optimum(OptParams P) {
   const int k = blockIdx.x;
   const int lane = static_cast<int>(threadIdx.x);
   Search S;
   S.nodes = 0;
-  S.cap = static_cast<int32_t>(P.node_cap < 0x7FFFFFFF ? P.node_cap : 0x7FFFFFFF);
   S.stop = false;
   Inst I;
   int status = setup(P, k, I, S);
   if (status == SCHED_OK && I.n > 0) {
-    if (fits_profile(I)) pplace<0, false>(slim(I), S, I.rem[0], 0, 0, lane, nullptr);
+    const bool profile = fits_profile(I);
+    const int64_t budget = profile ? P.node_cap : P.wide_cap;
+    S.cap = static_cast<int32_t>(budget < 0x7FFFFFFF ? budget : 0x7FFFFFFF);
+    if (profile) pplace<0, false>(slim(I), S, I.rem[0], 0, 0, lane, nullptr);
     else wplace<0, false>(I, S, 0, lane, nullptr);
-    if (S.stop) status = P.unfinished == kSplit && !fits_profile(I) ? kSplitWide : P.unfinished;
+    if (S.stop) status = P.unfinished == kSplit && !profile ? kSplitWide : P.unfinished;
   }
   if (status != SCHED_OK && status != SCHED_E_STEP_CAP && status != kSplit && status != kSplitWide) S.best = 0;
   if (lane == 0) {
@@ -631,7 +635,7 @@ extern "C" int sched_optimum(const sched_instances_t* in, int64_t M, const int64
   P.nodes = nodes;
   // a first launch with a short budget, then the unfinished instances on workgroups
   const bool split = cap > opt::kFirstPassNodes;
-  P.node_cap = cap;
+  P.node_cap = P.wide_cap = cap;
   P.unfinished = split ? opt::kSplit : SCHED_E_STEP_CAP;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   // the second launch's grid: as many workgroups as the device holds at once
@@ -650,8 +654,12 @@ extern "C" int sched_optimum(const sched_instances_t* in, int64_t M, const int64
     // late; the more rounds of waves, the more a larger budget saves there.  8
     // requests, budgets 2^12 and 2^17: 64 instances 0.93 and 7.0 ms, 4096 12.1
     // and 15.3 ms, 65536 156 and 112 ms; 2000 of 7 requests 2.6 and 8.4 ms.
+    // An instance that does not fit a profile keeps the full budget: below it the
+    // second launch goes through pairs of first starts, one by one in every wave,
+    // which takes longer than the nodes it saves.
     const int64_t rounds = (static_cast<int64_t>(P.K) + 16 * int64_t(n_cu) - 1) / (16 * int64_t(n_cu));
     P.node_cap = std::min(opt::kFirstPassNodes, (int64_t(1) << 12) * (rounds <= 1 ? 1 : 2 * rounds));
+    P.wide_cap = opt::kFirstPassNodes;
     if (per_cu < 1) per_cu = 1;
     if (per_cu_wide < 1) per_cu_wide = 1;
     // workspace: the counts, then four arrays of K entries

@@ -9,6 +9,7 @@ import pytest
 
 from oracle import oracle as O
 from paper_2508_14544_amd import workloads as W
+from opt_search import one_wave_search
 from test_gpu_optimum import B, gpu_opt  # noqa: F401  (B: the module's fixture)
 
 pytestmark = pytest.mark.gpu
@@ -66,3 +67,34 @@ def test_both_searches_in_the_second_launch(B):  # noqa: F811
     assert r["tel"].tolist() == [int(x["tel"][0]) for x in one]
     hsf = O.simulate_batch(b, O.HSF)["tel"]
     assert (r["tel"] <= hsf).all()
+
+
+def late_instances(count, late, seed, least, most):
+    """Instances of seven requests, six at step 0 and one at step `late`, that the
+    one-wave search ends after `least` to `most` start steps, with their optimum and
+    that number."""
+    rng = np.random.default_rng(seed)
+    found = []
+    while len(found) < count:
+        inst = {"arrival": [0] * 6 + [late], "prompt": rng.integers(0, 4, 7).tolist(),
+                "output": rng.integers(1, 7, 7).tolist()}
+        best, nodes, ended = one_wave_search(inst, 12, most)
+        if ended and nodes > least:
+            found.append((inst, best, nodes))
+    return found
+
+
+def test_late_arrivals_end_in_the_first_launch(B):  # noqa: F811
+    # beyond the profile a small batch has the whole first budget: every start step
+    # is one of the one-wave search's, also where node_cap allows few more.  (The
+    # six alone are over before the seventh comes, so the optima add up.)
+    found = late_instances(20, 300, 3, 1 << 12, 1 << 17)
+    b = W.from_lists(12, [i for i, _, _ in found], name="opt_late")
+    for cap in (0, (1 << 17) + 1):
+        r = gpu_opt(B, b, node_cap=cap)
+        assert (r["status"] == 0).all()
+        assert r["tel"].tolist() == [t for _, t, _ in found]
+        assert r["nodes"].tolist() == [c for _, _, c in found]
+    for inst, t, _ in found[:3]:
+        six = {f: inst[f][:6] for f in inst}
+        assert t == O.opt_tel(six, 12) + inst["output"][6]
