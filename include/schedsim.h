@@ -244,9 +244,9 @@ int sched_validate(const sched_instances_t* instances, int32_t algo, int64_t M, 
  * launch); the instances not finished by then are
  * searched again by a second launch of as many 16-wave workgroups as the
  * device holds at once, whose waves claim the pieces below the starts of an
- * instance's first two requests one at a time from any unfinished instance
- * (the first launch's best is the starting bound; best totals are shared in
- * global memory at every claim and in LDS within a workgroup), each wave with
+ * instance's first two requests (the first one of two) one at a time from any
+ * unfinished instance (the first launch's best is the starting bound; best totals are
+ * shared in global memory at every claim and in LDS within a workgroup), each wave with
  * at most node_cap nodes per instance it works on.  The second launch takes a
  * stream-ordered workspace of 16 bytes per instance (hipMallocAsync).  Reads
  * offsets, arrival (NULL = all 0), prompt and output of `instances`
@@ -260,9 +260,10 @@ int sched_validate(const sched_instances_t* instances, int32_t algo, int64_t M, 
  * SCHED_E_INVAL for bad offsets, SCHED_E_UNSUPPORTED when max a + sum(o + 1)
  * reaches 2^27, SCHED_E_STEP_CAP when a wave's search exceeded node_cap nodes
  * (total_latency then holds the best schedule found, an upper bound)), and,
- * if nodes is not NULL, nodes[K] searched (start steps tested, both launches).
- * node_cap <= 0 selects 2^26; larger
- * budgets are clamped to 2^31 - 1.  Returns SCHED_E_UNSUPPORTED if max_requests > 8 (nothing
+ * if nodes is not NULL, nodes[K] searched (start steps tested, both launches; where
+ * max a + sum(o + 1) + 1 + max o is above 63, those that a wave goes through to find
+ * its pieces count one for 64).  node_cap <= 0 selects 2^26; larger budgets are
+ * clamped to 2^31 - 2^16.  Returns SCHED_E_UNSUPPORTED if max_requests > 8 (nothing
  * queued), SCHED_E_INVAL for NULL pointers or M outside (0, 2^30). */
 int sched_optimum(const sched_instances_t* instances, int64_t M, const int64_t* upper_bound,
                   int64_t* total_latency, int32_t* status, int64_t* nodes, int64_t node_cap, void* stream);

@@ -81,9 +81,11 @@ constexpr int kSplit = -100, kSplitWide = -101;
 // most nodes of the first launch (one wave per instance); a call with a budget
 // up to this has no second launch
 constexpr int64_t kFirstPassNodes = int64_t(1) << 17;
-// waves of a second-launch workgroup, and the depth below which they split
+// waves of a second-launch workgroup
 constexpr int kGroupWaves = 16;
-constexpr int kSplitDepth = 2;
+// Most nodes of a wave, and pieces of an instance: the counters (int32) stay above it by
+// what one chunk of starts adds (64) and one claim for each of the waves of a launch.
+constexpr int32_t kMaxNodes = 0x7FFFFFFF - (1 << 16);
 constexpr int kFlagClaimed = 1, kFlagStop = 2, kFlagWide = 4;
 constexpr int kPoolHead = 2;  // words of the pool before its arrays
 
@@ -105,9 +107,49 @@ struct Search {
   int32_t c[kMaxN];         // completion step p + o of each placed run
   int32_t mem[kMaxN];
   int32_t best;             // below 8 * kHorizonLimit = 2^30
-  int32_t nodes, cap;       // the budget is clamped to 2^31 - 1
+  int32_t nodes, cap;       // cap <= kMaxNodes
   bool stop;
 };
+
+// Whether request D can start at step pd beside the placed runs 0..D-1, and the
+// memory at its completion (mend).
+template <int D>
+__device__ __forceinline__ bool start_fits(const Inst& I, const Search& S, int32_t pd, int32_t& mend) {
+  const int32_t end = pd + I.o[D];
+  bool ok = true;
+  mend = I.s[D] + I.o[D];
+#pragma unroll
+  for (int q = 0; q < D; ++q) {
+    const int32_t cq = S.c[q], pq = cq - I.o[q];
+    if (cq >= pd && cq <= end) ok = ok && S.mem[q] + I.s[D] + (cq - pd) <= I.M;
+    if (pq <= end && end <= cq) mend += I.s[q] + (end - pq);
+  }
+  return ok && mend <= I.M;
+}
+
+// Request D's run from step pj on (memory mj at its completion) joins the placed
+// runs, or leaves them.
+template <int D>
+__device__ __forceinline__ void place(const Inst& I, Search& S, int32_t pj, int32_t mj) {
+  const int32_t ej = pj + I.o[D];
+  S.c[D] = ej;
+#pragma unroll
+  for (int q = 0; q < D; ++q) {
+    const int32_t cq = S.c[q];
+    if (cq >= pj && cq <= ej) S.mem[q] += I.s[D] + (cq - pj);
+  }
+  S.mem[D] = mj;
+}
+
+template <int D>
+__device__ __forceinline__ void unplace(const Inst& I, Search& S, int32_t pj) {
+  const int32_t ej = pj + I.o[D];
+#pragma unroll
+  for (int q = 0; q < D; ++q) {
+    const int32_t cq = S.c[q];
+    if (cq >= pj && cq <= ej) S.mem[q] -= I.s[D] + (cq - pj);
+  }
+}
 
 // The search below a node at depth D (runs 0..D-1 placed at total cost
 // `cost`), the lanes of the wave testing 64 starts at a time.  SHARED: the
@@ -126,16 +168,8 @@ __device__ __forceinline__ void wplace(const Inst& I, Search& S, int32_t cost, i
       const int32_t pd = base + lane;
       const int32_t c = cost + (pd + I.o[D] - I.a[D]);
       const bool live = pd <= I.horizon && c + I.rem[D + 1] < S.best;
-      const int32_t end = pd + I.o[D];
-      bool ok = live;
-      int32_t mend = I.s[D] + I.o[D];
-#pragma unroll
-      for (int q = 0; q < D; ++q) {
-        const int32_t cq = S.c[q], pq = cq - I.o[q];
-        if (cq >= pd && cq <= end) ok = ok && S.mem[q] + I.s[D] + (cq - pd) <= I.M;
-        if (pq <= end && end <= cq) mend += I.s[q] + (end - pq);
-      }
-      ok = ok && mend <= I.M;
+      int32_t mend;
+      const bool ok = start_fits<D>(I, S, pd, mend) && live;
       uint64_t m = __builtin_amdgcn_ballot_w64(ok);
       const uint64_t lv = __builtin_amdgcn_ballot_w64(live);
       S.nodes += __builtin_popcountll(lv) + (lv != ~0ull ? 1 : 0);
@@ -156,21 +190,9 @@ __device__ __forceinline__ void wplace(const Inst& I, Search& S, int32_t cost, i
           }
           return;
         }
-        const int32_t ej = pj + I.o[D];
-        const int32_t mj = __builtin_amdgcn_readlane(mend, j);
-        S.c[D] = ej;
-#pragma unroll
-        for (int q = 0; q < D; ++q) {
-          const int32_t cq = S.c[q];
-          if (cq >= pj && cq <= ej) S.mem[q] += I.s[D] + (cq - pj);
-        }
-        S.mem[D] = mj;
+        place<D>(I, S, pj, __builtin_amdgcn_readlane(mend, j));
         wplace<D + 1, SHARED>(I, S, cj, lane, sb);
-#pragma unroll
-        for (int q = 0; q < D; ++q) {
-          const int32_t cq = S.c[q];
-          if (cq >= pj && cq <= ej) S.mem[q] -= I.s[D] + (cq - pj);
-        }
+        unplace<D>(I, S, pj);
         if (S.stop) return;
       }
       if (lv != ~0ull) return;
@@ -311,9 +333,10 @@ __device__ __forceinline__ void pplace(const Slim& I, Search& S, int32_t e, int3
   }
 }
 
-// wtop over the memory profile (n > kSplitDepth = 2): the same leaves in the
-// same order; the starts of the second request are one mask, so the leaves of
-// a first start that are all claimed are passed by their number.
+// wtop over the memory profile: the feasible starts of the first two requests (two
+// requests alone, at most 63 starts each, end within the first launch's 2^12 nodes
+// or more).  The starts of the second request are one mask, so the leaves of a
+// first start that are all claimed are passed by their number.
 __device__ __forceinline__ void ptop(const Slim& I, Search& S, int32_t e, int lane, int32_t* sb, int32_t* cnt,
                                      int32_t* gb, int32_t claim) {
   int32_t leaf = 0;
@@ -353,48 +376,61 @@ __device__ __forceinline__ void ptop(const Slim& I, Search& S, int32_t e, int la
   }
 }
 
-// The first kSplitDepth levels for the waves that share an instance: every
-// wave walks the same feasible starts of the first kSplitDepth requests
-// (without the bound's pruning, so that the walk, and the numbering of its
-// leaves, is the same in every wave) and searches below the leaves it claims:
-// a wave claims the next unclaimed leaf from the instance's counter in global
-// memory (*cnt) whenever it has searched below its last one, and at every
-// claim trades best totals with the instance's global best (*gb) and its
-// workgroup's (*sb).
-template <int D>
-__device__ __forceinline__ void wtop(const Inst& I, Search& S, int32_t cost, int lane, int32_t* sb, int32_t* cnt,
-                                     int32_t* gb, int32_t& leaf, int32_t& claim) {
+// The levels 0 to LEAF for the waves that share an instance: every wave goes
+// through the same feasible starts of the first LEAF + 1 requests, 64 at a time,
+// up to those whose cost reaches `first`, the total that the first launch left
+// (one number for all of them, so the numbering of the leaves is the same in every
+// wave), and searches below the leaves it claims: a wave claims the next
+// unclaimed leaf from the instance's counter in global memory (*cnt) whenever it
+// has searched below its last one, and at every claim trades best totals with
+// the instance's global best (*gb) and its workgroup's (*sb).  Once a start of
+// the first request reaches the best total no later leaf can improve it, whoever
+// claims it, and the wave is done.  64 starts gone through count as one node of
+// the wave's budget.
+// Without `first` a wave went through every start up to the horizon, one at a time:
+// 10^5 pairs where the last of seven requests arrives at step 300 and 10^10 at step
+// 100000, of which those below a bound of 60 are a few hundred.
+template <int D, int LEAF>
+__device__ __forceinline__ void wtop(const Inst& I, Search& S, int32_t first, int32_t cost, int lane, int32_t* sb,
+                                     int32_t* cnt, int32_t* gb, int32_t& leaf, int32_t& claim) {
   const int32_t lo = (D > 0 && ((I.same >> D) & 1u)) ? S.c[D > 0 ? D - 1 : 0] - I.o[D > 0 ? D - 1 : 0] : I.a[D];
-  for (int32_t pd = lo; pd <= I.horizon; ++pd) {
-    ++S.nodes;
+  for (int32_t base = lo; base <= I.horizon; base += 64) {
+    const int32_t pd = base + lane;
     const int32_t c = cost + (pd + I.o[D] - I.a[D]);
-    const int32_t end = pd + I.o[D];
-    bool ok = true;
-    int32_t mend = I.s[D] + I.o[D];
-#pragma unroll
-    for (int r = 0; r < D; ++r) {
-      const int32_t cr = S.c[r], pr = cr - I.o[r];
-      if (cr >= pd && cr <= end) ok = ok && S.mem[r] + I.s[D] + (cr - pd) <= I.M;
-      if (pr <= end && end <= cr) mend += I.s[r] + (end - pr);
-    }
-    if (!ok || mend > I.M) continue;
-    if (D == I.n - 1) {
-      // a complete schedule above the split (n <= kSplitDepth): the same in every wave
-      S.best = c < S.best ? c : S.best;
+    const bool live = pd <= I.horizon && c + I.rem[D + 1] < first;
+    int32_t mend;
+    const bool ok = start_fits<D>(I, S, pd, mend) && live;
+    uint64_t m = __builtin_amdgcn_ballot_w64(ok);
+    const uint64_t lv = __builtin_amdgcn_ballot_w64(live);
+    if (++S.nodes > S.cap || leaf > kMaxNodes) {
+      S.stop = true;
       return;
     }
-    S.c[D] = end;
-#pragma unroll
-    for (int r = 0; r < D; ++r) {
-      const int32_t cr = S.c[r];
-      if (cr >= pd && cr <= end) S.mem[r] += I.s[D] + (cr - pd);
+    if constexpr (D == LEAF) {
+      // (a wave's claim is never behind it)
+      const int32_t here = __builtin_popcountll(m);
+      if (claim - leaf >= here) {
+        leaf += here;
+        m = 0ull;
+      }
     }
-    S.mem[D] = mend;
-    if constexpr (D == kSplitDepth - 1) {
-      if (leaf == claim) {
-        const int32_t g = __hip_atomic_load(sb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        S.best = g < S.best ? g : S.best;
-        if (c + I.rem[D + 1] < S.best) wplace<D + 1, true>(I, S, c, lane, sb);
+    while (m) {
+      const int j = __builtin_ctzll(m);
+      m &= m - 1;
+      if (D == LEAF && leaf++ != claim) continue;
+      const int32_t g = __builtin_amdgcn_readfirstlane(
+          __hip_atomic_load(sb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+      S.best = g < S.best ? g : S.best;
+      const int32_t pj = base + j;
+      const int32_t cj = cost + (pj + I.o[D] - I.a[D]);
+      const int32_t mj = __builtin_amdgcn_readlane(mend, j);
+      const bool below = cj + I.rem[D + 1] < S.best;
+      if constexpr (D == LEAF) {
+        if (below) {
+          place<D>(I, S, pj, mj);
+          wplace<D + 1, true>(I, S, cj, lane, sb);
+          unplace<D>(I, S, pj);
+        }
         int32_t nx = 0, gbv = 0;
         if (lane == 0) {
           nx = atomicAdd(cnt, 1);
@@ -404,17 +440,15 @@ __device__ __forceinline__ void wtop(const Inst& I, Search& S, int32_t cost, int
         gbv = __builtin_amdgcn_readfirstlane(gbv);
         if (gbv < S.best) S.best = gbv;
         if (lane == 0) atomicMin(sb, S.best);
+      } else {
+        if (!below) return;
+        place<D>(I, S, pj, mj);
+        wtop<D + 1, LEAF>(I, S, first, cj, lane, sb, cnt, gb, leaf, claim);
+        unplace<D>(I, S, pj);
       }
-      ++leaf;
-    } else {
-      wtop<D + 1>(I, S, c, lane, sb, cnt, gb, leaf, claim);
+      if (S.stop) return;
     }
-#pragma unroll
-    for (int r = 0; r < D; ++r) {
-      const int32_t cr = S.c[r];
-      if (cr >= pd && cr <= end) S.mem[r] -= I.s[D] + (cr - pd);
-    }
-    if (S.stop) return;
+    if (lv != ~0ull) return;
   }
 }
 
@@ -513,7 +547,7 @@ __global__ __launch_bounds__(64) void k_optimum(OptParams P) {
   if (status == SCHED_OK && I.n > 0) {
     const bool profile = fits_profile(I);
     const int64_t budget = profile ? P.node_cap : P.wide_cap;
-    S.cap = static_cast<int32_t>(budget < 0x7FFFFFFF ? budget : 0x7FFFFFFF);
+    S.cap = static_cast<int32_t>(budget < kMaxNodes ? budget : kMaxNodes);
     if (profile) pplace<0, false>(slim(I), S, I.rem[0], 0, 0, lane, nullptr);
     else wplace<0, false>(I, S, 0, lane, nullptr);
     if (S.stop) status = P.unfinished == kSplit && !profile ? kSplitWide : P.unfinished;
@@ -576,7 +610,7 @@ __global__ __launch_bounds__(64 * kGroupWaves) void k_optimum_pool(OptParams P) 
       const int k = list[j];
       Search S;
       S.nodes = 0;
-      S.cap = static_cast<int32_t>(P.node_cap < 0x7FFFFFFF ? P.node_cap : 0x7FFFFFFF);
+      S.cap = static_cast<int32_t>(P.node_cap < kMaxNodes ? P.node_cap : kMaxNodes);
       S.stop = false;
       Inst I;
       (void)setup(P, k, I, S);  // valid: the first launch searched it
@@ -585,8 +619,13 @@ __global__ __launch_bounds__(64 * kGroupWaves) void k_optimum_pool(OptParams P) 
       if (lane == 0) first = atomicAdd(&cnt[j], 1);
       [[maybe_unused]] int32_t leaf = 0;
       int32_t claim = __builtin_amdgcn_readfirstlane(first);
-      if constexpr (WIDE) wtop<0>(I, S, 0, lane, &sbest, &cnt[j], &gbest[j], leaf, claim);
-      else ptop(slim(I), S, I.rem[0], lane, &sbest, &cnt[j], &gbest[j], claim);
+      if constexpr (WIDE) {
+        // (one request alone ends in the first launch; the total is the first launch's
+        // until k_pool_finish)
+        const int32_t total = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(P.total_latency[k]));
+        if (I.n > 2) wtop<0, 1>(I, S, total, 0, lane, &sbest, &cnt[j], &gbest[j], leaf, claim);
+        else wtop<0, 0>(I, S, total, 0, lane, &sbest, &cnt[j], &gbest[j], leaf, claim);
+      } else ptop(slim(I), S, I.rem[0], lane, &sbest, &cnt[j], &gbest[j], claim);
       if (lane == 0) {
         atomicMin(&gbest[j], S.best);
         if (P.nodes) atomicAdd(reinterpret_cast<unsigned long long*>(&P.nodes[k]),

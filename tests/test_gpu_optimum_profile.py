@@ -1,9 +1,9 @@
 """GPU parity of the hindsight optimum's two searches at the line between them: a
 memory profile of 64 steps where the horizon (max a + sum(o + 1) + 1) plus the
 longest output is at most 63, the placed runs' tests above.  Against the oracle's
-independent search, with late arrivals, runs that fill the profile, identical
-requests, and both kinds in one batch under a budget that leaves some of them to
-the second launch."""
+independent search and a plain model of the one-wave one, with late arrivals, runs
+that fill the profile, identical requests, and instances of both kinds that the first
+launch ends and that it leaves to the second."""
 import numpy as np
 import pytest
 
@@ -11,6 +11,7 @@ from oracle import oracle as O
 from paper_2508_14544_amd import workloads as W
 from opt_search import one_wave_search
 from test_gpu_optimum import B, gpu_opt  # noqa: F401  (B: the module's fixture)
+from test_oracle_pins import spt_single_machine_tel
 
 pytestmark = pytest.mark.gpu
 
@@ -48,36 +49,15 @@ def test_one_long_run_fills_the_profile(B):  # noqa: F811
     assert r["tel"].tolist() == [O.opt_tel(b.instance(k), b.M) for k in range(b.num_instances)]
 
 
-def test_both_searches_in_the_second_launch(B):  # noqa: F811
-    # the same eight requests with and without a late ninth step count: the
-    # optimum of a batch that mixes both searches equals the one-instance calls'
-    rng = np.random.default_rng(8)
-    insts = []
-    for _ in range(6):
-        o = rng.integers(4, 7, 7)
-        insts.append({"arrival": [0] * 7, "prompt": rng.integers(1, 4, 7).tolist(), "output": o.tolist()})
-        insts.append(dict(insts[-1], arrival=[0] * 6 + [40]))
-    b = W.from_lists(12, insts, name="opt_mixed")
-    steps = [max(i["arrival"]) + sum(i["output"]) + 7 + 1 + max(i["output"]) for i in insts]
-    assert min(steps) <= 63 < max(steps)
-    r = gpu_opt(B, b)
-    assert (r["status"] == 0).all()
-    assert (r["nodes"] > 1 << 12).any()      # beyond the first launch's budget of so small a batch
-    one = [gpu_opt(B, W.from_lists(12, [i], name="opt_one")) for i in insts]
-    assert r["tel"].tolist() == [int(x["tel"][0]) for x in one]
-    hsf = O.simulate_batch(b, O.HSF)["tel"]
-    assert (r["tel"] <= hsf).all()
-
-
-def late_instances(count, late, seed, least, most):
-    """Instances of seven requests, six at step 0 and one at step `late`, that the
-    one-wave search ends after `least` to `most` start steps, with their optimum and
-    that number."""
+def late_instances(count, late, seed, least, most, n=7, o=(1, 6)):
+    """Instances of n requests, the last one at step `late` and the others at step 0,
+    that the one-wave search ends after `least` to `most` start steps, with their
+    optimum and that number."""
     rng = np.random.default_rng(seed)
     found = []
     while len(found) < count:
-        inst = {"arrival": [0] * 6 + [late], "prompt": rng.integers(0, 4, 7).tolist(),
-                "output": rng.integers(1, 7, 7).tolist()}
+        inst = {"arrival": [0] * (n - 1) + [late], "prompt": rng.integers(0, 4, n).tolist(),
+                "output": rng.integers(o[0], o[1] + 1, n).tolist()}
         best, nodes, ended = one_wave_search(inst, 12, most)
         if ended and nodes > least:
             found.append((inst, best, nodes))
@@ -98,3 +78,53 @@ def test_late_arrivals_end_in_the_first_launch(B):  # noqa: F811
     for inst, t, _ in found[:3]:
         six = {f: inst[f][:6] for f in inst}
         assert t == O.opt_tel(six, 12) + inst["output"][6]
+
+
+@pytest.mark.parametrize("late", [300, 2000, 1 << 20])
+def test_late_arrivals_in_the_second_launch(B, late):  # noqa: F811
+    # beyond the profile and the first budget: what the waves go through to find their
+    # pieces is a matter of the bound, not of the horizon, so the nodes stay within a
+    # few of the one-wave search's for each of the device's waves
+    import torch
+    found = late_instances(3, late, 4, 1 << 17, 1 << 20, n=8, o=(2, 6))
+    b = W.from_lists(12, [i for i, _, _ in found], name="opt_late_pool")
+    r = gpu_opt(B, b)
+    assert (r["status"] == 0).all()
+    assert r["tel"].tolist() == [t for _, t, _ in found]
+    assert (r["nodes"] > 1 << 17).all()
+    waves = 32 * torch.cuda.get_device_properties(0).multi_processor_count
+    assert (r["nodes"] < [4 * c + 100 * waves for _, _, c in found]).all()
+
+
+def test_long_runs_in_the_second_launch(B):  # noqa: F811
+    # two requests (pieces are starts of the first one), three and four, one at a time
+    outs = [[900, 700], [600, 611], [300, 200, 250], [150, 150, 150], [60, 50, 40, 30]]
+    insts = [{"prompt": [1000] * len(o), "output": o} for o in outs]
+    assert all(one_wave_search(i, 1999, 1 << 17)[2] is False for i in insts)
+    r = gpu_opt(B, W.from_lists(1999, insts, name="opt_long_pool"))
+    assert (r["status"] == 0).all()
+    assert r["tel"].tolist() == [spt_single_machine_tel(o) for o in outs]
+    # a budget that the walk over the pieces uses up ends the search, with a bound
+    o = [30000, 30000, 30000]
+    r = gpu_opt(B, W.from_lists(1 << 16, [{"prompt": [1 << 15] * 3, "output": o}], name="opt_long_cap"),
+                node_cap=(1 << 17) + 64)
+    assert r["status"].tolist() == [O.E_STEP_CAP] and r["tel"][0] >= spt_single_machine_tel(o)
+
+
+def test_both_searches_in_the_second_launch(B):  # noqa: F811
+    # a batch with instances of both kinds beyond their first budgets
+    rng = np.random.default_rng(8)
+    found = []
+    while len(found) < 6:
+        i = {"arrival": [0] * 7, "prompt": rng.integers(1, 4, 7).tolist(), "output": rng.integers(4, 7, 7).tolist()}
+        best, nodes, ended = one_wave_search(i, 12, 1 << 20)
+        if ended and nodes > 1 << 13 and sum(i["output"]) + 7 + 1 + max(i["output"]) < 64:
+            found.append((i, best, 1 << 12))
+    found += [(i, t, 1 << 17) for i, t, _ in late_instances(4, 500, 9, 1 << 17, 1 << 20, n=8, o=(2, 6))]
+    found = [found[k] for k in rng.permutation(len(found))]
+    b = W.from_lists(12, [i for i, _, _ in found], name="opt_mixed")
+    r = gpu_opt(B, b)
+    assert (r["status"] == 0).all()
+    assert r["tel"].tolist() == [t for _, t, _ in found]
+    assert (r["nodes"] > [c for _, _, c in found]).all()
+    assert (r["tel"] <= O.simulate_batch(b, O.HSF)["tel"]).all()
