@@ -705,8 +705,9 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
   if (P.order) hipLaunchKernelGGL(sk::k_order_clear, dim3(1), dim3(sk::kOrderBuckets), 0, st, P);
   {
     const PrepareLaunch pl = prepare_launch(algo, nmax, in->num_instances, n_cu, tie, lds_max);
-    // (above 64 KiB a kernel's LDS has to be asked for)
-    if (pl.lds > 49152)
+    // (above 64 KiB a kernel's LDS has to be asked for: the buffers and what the kernel
+    // itself declares, at most PrepareShared<16>)
+    if (pl.lds + sizeof(sk::PrepareShared<16>) > 65536)
       err = hipFuncSetAttribute(pl.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(pl.lds));
     void* args[] = {&P};
     if (err == hipSuccess) err = hipLaunchKernel(pl.kernel, dim3(P.K), dim3(64 * pl.waves), args, pl.lds, st);

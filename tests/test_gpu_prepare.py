@@ -29,7 +29,8 @@ def B():
 
 
 @pytest.mark.parametrize("algo", POLICIES)
-@pytest.mark.parametrize("n,count", [(64, 3), (65, 3), (256, 2), (300, 600), (4096, 2), (4097, 2), (12300, 1), (18500, 1)])
+@pytest.mark.parametrize("n,count", [(64, 3), (65, 3), (256, 2), (300, 600), (4096, 2), (4097, 2), (6100, 1),
+                                     (12200, 1), (12300, 1), (18500, 1)])
 def test_sizes(B, n, count, algo):
     few = n > 4000  # lengths that keep the simulation of a large instance short
     b = make(400 if few else 900, n, count, n, o=(1, 6) if few else (1, 400), lower="all" if few else "half",
