@@ -267,6 +267,7 @@ __global__ __launch_bounds__(64 * W) void k_prepare(Params P) {
   const bool tie = P.tie_key != nullptr;
   uint32_t* const ka = LDS ? pre_buf : P.sort_a + b;
   uint32_t* const kb = LDS ? pre_buf + P.max_requests : P.sort_b + b;
+  if (P.retry_count && k == 0 && tid < kRetryCounts) P.retry_count[tid] = 0;
 
   // ---- checks; per-request outputs start as "not completed, never cancelled"
   // (with tie keys, the staging arrays the kernels write too); without tie keys,

@@ -79,6 +79,20 @@ __global__ __launch_bounds__(256) void k_prio_classes(Params P) {
     for (int k = threadIdx.x; k < P.K; k += 256) P.pclass[k] = -1;
 }
 
+// The instances that a retry pass takes, in no particular order (algo: the policy
+// of the pass, in adaptive runs).
+__global__ __launch_bounds__(256) void k_retry_list(Params P, int algo) {
+  const int k = blockIdx.x * 256 + static_cast<int>(threadIdx.x);
+  const int lane = static_cast<int>(threadIdx.x & 63u);
+  const bool take = k < P.K && !(P.algo_of && P.algo_of[k] != algo) && retry_takes(P, P.status[k]);
+  const uint64_t m = __builtin_amdgcn_ballot_w64(take);
+  if (m == 0) return;
+  int base = 0;
+  if (lane == 0) base = atomicAdd(&P.retry_count[0], __builtin_popcountll(m));
+  base = __builtin_amdgcn_readfirstlane(base);
+  if (take) P.retry_list[base + __builtin_popcountll(m & ((1ull << lane) - 1ull))] = k;
+}
+
 // Launch order (A_min batches served in several rounds of waves): the
 // instances by decreasing key, so that the longest expected simulations are
 // not the last ones to start.  The order within a bucket is whatever the
@@ -129,7 +143,9 @@ __global__ __launch_bounds__(256) void k_order_scatter(Params P) {
 // that hipGetSymbolAddress returns, taken once per device.
 // ---------------------------------------------------------------------------
 constexpr size_t kScratchBytes = size_t(96) << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// (beyond a call's workspace, the retry passes' counts)
+constexpr size_t kRetryBytes = 4 * sk::kRetryCounts;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kRetryBytes];
 
 // ---------------------------------------------------------------------------
 // host side: the C ABI
@@ -170,6 +186,7 @@ struct Tier {
   int gw;           // > 1: a workgroup of gw waves per instance (k_simulate_group)
   int grid;         // workgroups of the launch (0: one per instance)
   int roomy;        // the narrow ladder with 256 VGPRs (k_simulate_ladder_roomy)
+  int list;         // a retry pass over a list of the instances that it takes (k_retry_list)
 };
 
 // The workgroup kernels that exist (sched_group.hip), else NULL.
@@ -607,10 +624,17 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
         group_words = std::max<int64_t>(group_words, per * t.grid);
       } else {
         any_global = any_global || t.vglobal;
-        // (a retry pass has few instances to take, often none: its workgroups look
-        // through the statuses instead of being started for one each, 200 us for
-        // the 65536 of a sweep)
-        if (t.gw > 1 && t.retry) t.grid = static_cast<int>(std::min<int64_t>(in->num_instances, 16 * int64_t(n_cu)));
+      }
+      // A retry pass takes few of the instances of a large batch, often none, and a
+      // workgroup started for each of them costs 200 us at 65536.  A grid that the
+      // device holds at once (two or three workgroups a CU) goes through a list of
+      // them instead, also where many need it: 65536 instances of which every 4096th,
+      // every 256th or one in 20 runs 1200 requests at once, H-SF: 4.1, 5.9 and 37 ms;
+      // a workgroup an instance 7.2, 89 and 73 (the device gives workgroups to its XCDs
+      // in turn), 4096 workgroups with fixed shares 44, 89 and 45.
+      if (t.gw > 1 && t.run_mask != 0 && in->num_instances > 16 * int64_t(n_cu)) {
+        t.list = 1;
+        t.grid = std::min(t.grid > 0 ? t.grid : INT32_MAX, 4 * n_cu);
       }
       if (t.gw > 1 && !sim_kernel_any(sim_algos[a], t)) return SCHED_E_UNSUPPORTED;
     }
@@ -672,7 +696,7 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
   void* ws = nullptr;
   if (no_alloc) {
     if (scratch_address(dev, &ws) != hipSuccess) return SCHED_E_HIP;
-  } else if (hipMallocAsync(&ws, off, st) != hipSuccess) {
+  } else if (hipMallocAsync(&ws, off + kRetryBytes, st) != hipSuccess) {
     return SCHED_E_HIP;
   }
   char* base = static_cast<char*>(ws);
@@ -697,6 +721,9 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
   P.order = ord && ladder ? reinterpret_cast<int32_t*>(base + o_or) : nullptr;
   P.okey = P.order ? P.order + K : nullptr;
   P.obucket = P.order ? P.okey + K : nullptr;
+  for (int a = 0; a < n_sim; ++a)
+    for (int p = 0; p < n_tiers[a]; ++p)
+      if (tiers[a][p].list) P.retry_count = reinterpret_cast<int32_t*>(base + off);
   P.nw_max = nw;
   P.nw1_max = nw1;
   P.run_cap = forced_rows > 0 ? forced_rows * 64 : INT32_MAX;
@@ -766,11 +793,20 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
       q.retry_v_status = t.v_status;
       q.run_mask = t.run_mask;
       q.stage_comp = t.stage;
+      if (t.list) {
+        // (the sort buffer is free now; every listed instance has more than 640 requests,
+        // and the adaptive policy's two run at the same time)
+        q.retry_list = reinterpret_cast<int32_t*>(P.sort_a) + (a == 1 ? N / 2 : 0);
+        q.retry_count = P.retry_count + 2 * (8 * a + p);
+        hipLaunchKernelGGL(sk::k_retry_list, dim3((P.K + 255) / 256), dim3(256), 0, sa, q, sim_algos[a]);
+        err = hipGetLastError();
+      }
       void* args[] = {&q};
       const dim3 tgrid(t.grid > 0 ? t.grid : P.K), tblock(64 * (t.gw > 1 ? t.gw : 1));
       // (a launch over every instance may take them in the launch order)
-      err = hipLaunchKernel(sim_kernel_any(sim_algos[a], t, P.order && t.grid <= 0, P.pclass != nullptr, rounds), tgrid,
-                            tblock, args, lds_of(a, t), sa);
+      if (err == hipSuccess)
+        err = hipLaunchKernel(sim_kernel_any(sim_algos[a], t, P.order && t.grid <= 0, P.pclass != nullptr, rounds),
+                              tgrid, tblock, args, lds_of(a, t), sa);
     }
   }
   if (side) {

@@ -123,6 +123,10 @@ struct Params {
   int32_t* order;
   int32_t* okey;
   int32_t* obucket;
+  // retry passes of fewer workgroups than instances: the instances that the pass
+  // takes, their number, and a cursor over them (NULL: workgroup g takes g, g + grid, ...)
+  int32_t* retry_list;
+  int32_t* retry_count;  // [0] the number, [1] the cursor
 };
 
 // Whether some request of the instance of n > 0 requests from b on arrives after
@@ -132,6 +136,9 @@ __device__ __forceinline__ bool late_arrivals(const Params& P, const int64_t b, 
   return P.arrival && P.arrival[b + n - 1] > 0;
 }
 
+// words of the retry passes' counts: two a pass, eight passes a policy, two policies
+constexpr int kRetryCounts = 32;
+
 // buckets of the launch-order key
 constexpr int kOrderBuckets = 64;
 
@@ -140,6 +147,11 @@ constexpr int kOrderBuckets = 64;
 // later pass simulates it again from step 0 with more room.
 constexpr int kRetryRows = -100;
 constexpr int kRetryV = -101;
+
+// Whether a retry pass takes an instance of this status.
+__device__ __forceinline__ bool retry_takes(const Params& P, const int status) {
+  return (status == kRetryRows && (P.run_mask & 1)) || (status == kRetryV && (P.run_mask & 2));
+}
 
 // ---------------------------------------------------------------------------
 // k_simulate
@@ -1241,15 +1253,28 @@ __device__ __forceinline__ void sim_instance(const Params& P, const int k, const
 // instances an earlier pass handed over run.
 // Workgroup g simulates instances g, g + grid, ... (a launch with global
 // cancelled sets has fewer workgroups than instances: each workgroup's sets
-// are its own).
+// are its own), or with P.retry_list the next one of the list until none is left:
+// which instances of a batch need a retry pass may follow any pattern (a sweep has its
+// parameters in blocks), and each takes milliseconds.
 template <int ALGO, int W, int ROWS, bool VGLOBAL>
 __global__ __launch_bounds__(64 * W) void k_simulate_group(Params P) {
-  for (int k = blockIdx.x; k < P.K; k += gridDim.x) {
-    if (P.algo_of && P.algo_of[k] != ALGO) continue;
+  extern __shared__ uint64_t lds64[];
+  const bool listed = P.retry_list != nullptr;
+  for (int g = blockIdx.x;; g += gridDim.x) {
+    int k = g;
+    if (listed) {
+      if (threadIdx.x == 0) lds64[0] = static_cast<uint64_t>(atomicAdd(&P.retry_count[1], 1));
+      __syncthreads();
+      k = wave::uniform(static_cast<int32_t>(lds64[0]));
+      __syncthreads();  // the instance uses the LDS
+      if (k >= P.retry_count[0]) return;
+      k = P.retry_list[k];
+    }
+    if (k >= P.K) return;
+    if (!listed && P.algo_of && P.algo_of[k] != ALGO) continue;
     int st0 = P.status[k];
     if (P.run_mask) {
-      const bool take = (st0 == kRetryRows && (P.run_mask & 1)) || (st0 == kRetryV && (P.run_mask & 2));
-      if (!take) continue;
+      if (!listed && !retry_takes(P, st0)) continue;
       st0 = SCHED_OK;
     }
     sim_instance<ALGO, ROWS, VGLOBAL, W>(P, k, st0, P.retry_status);

@@ -1280,8 +1280,7 @@ __global__ __launch_bounds__(64) void k_simulate(Params P) {
   if (P.algo_of && P.algo_of[k] != ALGO) return;  // adaptive run: the other policy's instance
   int st0 = P.status[k];
   if (RETRY_PASS) {
-    const bool take = (st0 == kRetryRows && (P.run_mask & 1)) || (st0 == kRetryV && (P.run_mask & 2));
-    if (!take) return;
+    if (!retry_takes(P, st0)) return;
     st0 = SCHED_OK;
   }
   WaveState st;
@@ -1304,8 +1303,7 @@ __device__ __forceinline__ void ladder_instance(const Params& P, const int k) {
   if constexpr (WIDE) {
     if (P.run_mask) {
       // a retry pass: only the instances an earlier pass handed over
-      const bool take = (st0 == kRetryRows && (P.run_mask & 1)) || (st0 == kRetryV && (P.run_mask & 2));
-      if (!take) return;
+      if (!retry_takes(P, st0)) return;
       st0 = SCHED_OK;
     }
   }

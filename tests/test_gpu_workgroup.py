@@ -205,3 +205,44 @@ def test_workgroup_statuses_and_empty_instances(B, ww):
             assert np.array_equal(g[f], g1[f]), (algo, f)
         ok = [k for k in range(batch.num_instances) if g["status"][k] == 0]
         assert_parity(batch, g, oracle_run(batch, algo, instances=ok), instances=ok)
+
+
+@pytest.mark.parametrize("algo", ["amax", "amin", "hsf", "aell", "adaptive", "arandom"])
+def test_retries_of_a_large_batch(B, algo):
+    # more instances than the device holds: the workgroup passes take theirs from a
+    # list.  Instances of 700, 1100 and 4300 runs at once (the wide ladder, four and
+    # eight waves) in blocks, 4096 apart and last, among short ones
+    import torch
+    a = O.ALGOS[algo]
+    K = 16 * torch.cuda.get_device_properties(0).multi_processor_count + 150
+    rng = np.random.default_rng(12)
+    large = {7: 1100, 7 + 4096: 1100, 8: 700, 9: 1100, 10: 4300, 11: 1100, K // 2: 4300, K - 2: 700, K - 1: 1100}
+    insts = []
+    for k in range(K):
+        n = large.get(k, 0 if k % 50 == 1 else 5)
+        o = rng.integers(1, 4 if n == 4300 else 13, n)
+        half = (o + 1) // 2 if k % 2 and k not in large else o  # (A_l would start those again)
+        # (the adaptive policy runs two of the large ones as A_l)
+        upper = 3 * o if algo == "adaptive" and k in (11, K // 2) else o + k % 2
+        insts.append({"arrival": [0] * n, "prompt": rng.integers(0, 2, n), "output": o, "lower": half, "upper": upper,
+                      "priority": rng.permutation(n)})
+    # (those of 4300 runs, for which the oracle takes long, have the closed form: all
+    # requests start at step 0 and end as they are)
+    ks = [k for k in sorted(large) if large[k] < 4300] + list(range(0, K, 97))
+    wide = [k for k in sorted(large) if large[k] == 4300]
+    for b in (W.from_lists(16384, insts, name="retry_list"), W.with_tie_keys(W.from_lists(16384, insts, name="retry_list_ties"), 3)):
+        ref = oracle_run(b, a, instances=ks)
+        at_once = {k: int((g_["completion"] == insts[k]["output"]).sum())
+                   for k in ks if k in large for g_ in [oracle_run(b, a, instances=[k])]}
+        assert {k: n > 1024 for k, n in at_once.items()} == {k: large[k] == 1100 for k in at_once}
+        for no_alloc in (False, True):
+            g = gpu_run(B, b, a, no_alloc=no_alloc)
+            assert (g["status"] == 0).all()
+            assert_parity(b, g, ref, instances=ks)
+            for k in wide:
+                o = insts[k]["output"]
+                assert np.array_equal(g["completion"][b.offsets[k]:b.offsets[k + 1]], o)
+                assert not g["evictions"][b.offsets[k]:b.offsets[k + 1]].any()
+                assert [int(g[f][k]) for f in ("tel", "request_steps", "makespan")] == [o.sum(), o.sum(), o.max()]
+    if algo == "adaptive":
+        assert g["algo_used"][[7, 11, K // 2]].tolist() == [O.AMIN, O.AELL, O.AELL]
