@@ -80,7 +80,8 @@ __global__ __launch_bounds__(256) void k_prio_classes(Params P) {
 }
 
 // The instances that a retry pass takes, in no particular order (algo: the policy
-// of the pass, in adaptive runs).
+// of the pass, in adaptive runs).  All are counted, those that the list has room for
+// are listed.
 __global__ __launch_bounds__(256) void k_retry_list(Params P, int algo) {
   const int k = blockIdx.x * 256 + static_cast<int>(threadIdx.x);
   const int lane = static_cast<int>(threadIdx.x & 63u);
@@ -90,7 +91,8 @@ __global__ __launch_bounds__(256) void k_retry_list(Params P, int algo) {
   int base = 0;
   if (lane == 0) base = atomicAdd(&P.retry_count[0], __builtin_popcountll(m));
   base = __builtin_amdgcn_readfirstlane(base);
-  if (take) P.retry_list[base + __builtin_popcountll(m & ((1ull << lane) - 1ull))] = k;
+  const int at = base + __builtin_popcountll(m & ((1ull << lane) - 1ull));
+  if (take && at < P.retry_room) P.retry_list[at] = k;
 }
 
 // Launch order (A_min batches served in several rounds of waves): the
@@ -794,9 +796,11 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
       q.run_mask = t.run_mask;
       q.stage_comp = t.stage;
       if (t.list) {
-        // (the sort buffer is free now; every listed instance has more than 640 requests,
-        // and the adaptive policy's two run at the same time)
+        // (the sort buffer is free now and has room for them: every listed instance has
+        // more than 640 requests, of its own unless offsets decrease; the adaptive
+        // policy's two passes run at the same time)
         q.retry_list = reinterpret_cast<int32_t*>(P.sort_a) + (a == 1 ? N / 2 : 0);
+        q.retry_room = static_cast<int32_t>(std::min<size_t>(n_sim == 2 ? N / 2 : N, INT32_MAX));
         q.retry_count = P.retry_count + 2 * (8 * a + p);
         hipLaunchKernelGGL(sk::k_retry_list, dim3((P.K + 255) / 256), dim3(256), 0, sa, q, sim_algos[a]);
         err = hipGetLastError();

@@ -127,6 +127,7 @@ struct Params {
   // takes, their number, and a cursor over them (NULL: workgroup g takes g, g + grid, ...)
   int32_t* retry_list;
   int32_t* retry_count;  // [0] the number, [1] the cursor
+  int32_t retry_room;    // entries that the list holds
 };
 
 // Whether some request of the instance of n > 0 requests from b on arrives after
@@ -1255,11 +1256,12 @@ __device__ __forceinline__ void sim_instance(const Params& P, const int k, const
 // cancelled sets has fewer workgroups than instances: each workgroup's sets
 // are its own), or with P.retry_list the next one of the list until none is left:
 // which instances of a batch need a retry pass may follow any pattern (a sweep has its
-// parameters in blocks), and each takes milliseconds.
+// parameters in blocks), and each takes milliseconds.  A list too short for them (only
+// where offsets that decrease give the same requests to many instances) is not used.
 template <int ALGO, int W, int ROWS, bool VGLOBAL>
 __global__ __launch_bounds__(64 * W) void k_simulate_group(Params P) {
   extern __shared__ uint64_t lds64[];
-  const bool listed = P.retry_list != nullptr;
+  const bool listed = P.retry_list != nullptr && P.retry_count[0] <= P.retry_room;
   for (int g = blockIdx.x;; g += gridDim.x) {
     int k = g;
     if (listed) {

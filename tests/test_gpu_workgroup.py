@@ -246,3 +246,27 @@ def test_retries_of_a_large_batch(B, algo):
                 assert [int(g[f][k]) for f in ("tel", "request_steps", "makespan")] == [o.sum(), o.sum(), o.max()]
     if algo == "adaptive":
         assert g["algo_used"][[7, 11, K // 2]].tolist() == [O.AMIN, O.AELL, O.AELL]
+
+
+@pytest.mark.parametrize("algo", ["hsf", "adaptive"])
+def test_more_retries_than_requests(B, algo):
+    # offsets that go back and forth give the same 1200 requests to every other instance
+    # (the others have decreasing offsets): more instances for the workgroup passes than
+    # their list, which is as long as the batch has requests, holds
+    import torch
+    K = 16 * torch.cuda.get_device_properties(0).multi_processor_count + 150
+    n = 1200
+    assert K // 2 > n
+    rng = np.random.default_rng(5)
+    o = rng.integers(1, 13, n)
+    one = W.from_lists(16384, [{"arrival": [0] * n, "prompt": rng.integers(0, 2, n), "output": o, "lower": o,
+                                "upper": 3 * o}], name="retry_room")
+    db = B.to_device(one)
+    db.offsets = torch.tensor([0, n] * (K // 2) + [0], device=db.offsets.device)
+    out = B.simulate(db, B.ALGOS[algo])
+    torch.cuda.synchronize()
+    g = {f: v.cpu().numpy() for f, v in out.items()}
+    assert g["status"].tolist() == [0, B.E_INVAL] * (K // 2)
+    assert np.array_equal(g["completion"], o) and not g["evictions"].any()
+    assert (g["tel"].reshape(-1, 2) == [o.sum(), 0]).all() and (g["makespan"].reshape(-1, 2) == [o.max(), 0]).all()
+    assert (g["request_steps"].reshape(-1, 2) == [o.sum(), 0]).all()
