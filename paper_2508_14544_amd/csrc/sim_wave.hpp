@@ -1266,7 +1266,6 @@ __device__ __forceinline__ void finish_instance(const Params& P, const int k, co
 #undef SK_LOAD_ARRIVALS
 #undef SK_F_FIND
 #undef SK_V_INSERT
-#undef SK_PEND_INSERT
 #undef SK_Q_WINDOW
 #undef SK_AT_ROW
 #undef SK_DROP_SHARE
@@ -1292,20 +1291,17 @@ __global__ __launch_bounds__(64) void k_simulate(Params P) {
 
 // One wave per instance on the row ladder: the simulation starts with 2
 // register rows and moves, state and all, to the body with 3, 5, 8 or 10 rows
-// as its running set grows and back down as it shrinks, so that every scan
-// covers about as many rows as the instance has runs (most of an instance's
-// events happen with at most 128 runs).  A running set beyond 640 runs ends
-// with P.retry_status.  Held to 128 VGPRs so that four waves share a SIMD.
-template <int ALGO, bool WIDE>
-__device__ __forceinline__ void ladder_instance(const Params& P, const int k) {
+// (the wide ladder, below: also 12 and 16) as its running set grows and back down
+// as it shrinks, so that every scan covers about as many rows as the instance has
+// runs (most of an instance's events happen with at most 128 runs).
+template <int ALGO>
+__device__ __forceinline__ void wide_ladder_instance(const Params& P, const int k) {
   if (P.algo_of && P.algo_of[k] != ALGO) return;
   int st0 = P.status[k];
-  if constexpr (WIDE) {
-    if (P.run_mask) {
-      // a retry pass: only the instances an earlier pass handed over
-      if (!retry_takes(P, st0)) return;
-      st0 = SCHED_OK;
-    }
+  if (P.run_mask) {
+    // a retry pass: only the instances an earlier pass handed over
+    if (!retry_takes(P, st0)) return;
+    st0 = SCHED_OK;
   }
   int arr_ptr = 0;
   if (st0 == SCHED_OK) {
@@ -1333,33 +1329,21 @@ __device__ __forceinline__ void ladder_instance(const Params& P, const int k) {
     }
     return;
   }
-  using ST = typename std::conditional<WIDE, WaveStateWide, WaveState>::type;
+  using ST = WaveStateWide;
   ST st;
   fresh_state(st, arr_ptr);
   int r;
-  if constexpr (!WIDE) {
-    do {
-      switch (st.next_rows) {
-        case 2: r = wave_instance<ALGO, 2, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 3: r = wave_instance<ALGO, 3, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 5: r = wave_instance<ALGO, 5, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 8: r = wave_instance<ALGO, 8, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        default: r = wave_instance<ALGO, 10, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-      }
-    } while (r == kResume);
-  } else {
-    do {
-      switch (st.next_rows) {
-        case 2: r = wave_instance<ALGO, 2, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 3: r = wave_instance<ALGO, 3, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 5: r = wave_instance<ALGO, 5, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 8: r = wave_instance<ALGO, 8, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 10: r = wave_instance<ALGO, 10, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        case 12: r = wave_instance<ALGO, 12, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-        default: r = wave_instance<ALGO, 16, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
-      }
-    } while (r == kResume);
-  }
+  do {
+    switch (st.next_rows) {
+      case 2: r = wave_instance<ALGO, 2, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
+      case 3: r = wave_instance<ALGO, 3, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
+      case 5: r = wave_instance<ALGO, 5, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
+      case 8: r = wave_instance<ALGO, 8, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
+      case 10: r = wave_instance<ALGO, 10, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
+      case 12: r = wave_instance<ALGO, 12, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
+      default: r = wave_instance<ALGO, 16, true, true, false, false, ST>(P, k, SCHED_OK, P.retry_status, &st); break;
+    }
+  } while (r == kResume);
   finish_instance(P, k, SCHED_OK, r, st.rsteps, st.tot_ev, false);
 }
 
@@ -1368,7 +1352,7 @@ __device__ __forceinline__ void ladder_instance(const Params& P, const int k) {
 // instance P.order[g]; CLS_: issue priorities by P.pclass; PRIO_ false: the
 // waves keep the default issue priority, for batches in which priorities
 // cannot help (a wave per SIMD, or rounds of waves) but would cost scalar
-// instructions).
+// instructions).  A running set beyond 640 runs ends with P.retry_status.
 #define SK_NARROW_LADDER(ORDERED_, CLS_, PRIO_)                                                                                               \
   const int k = (ORDERED_) ? P.order[blockIdx.x] : static_cast<int>(blockIdx.x);                                                       \
   if (P.algo_of && P.algo_of[k] != ALGO) return;                                                                                       \
@@ -1434,7 +1418,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 // the narrow ladder (a retry pass).
 template <int ALGO>
 __global__ __launch_bounds__(64) void k_simulate_ladder_wide(Params P) {
-  ladder_instance<ALGO, true>(P, blockIdx.x);
+  wide_ladder_instance<ALGO>(P, blockIdx.x);
 }
 
 // The one-wave kernels of a policy, each policy's in a translation unit of its

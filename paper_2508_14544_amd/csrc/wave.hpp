@@ -1,10 +1,11 @@
 // wave.hpp -- wave64 primitives for gfx950 (CDNA4).
 //
-// 32-bit reductions first fold the four 16-lane rows onto each other with the
-// gfx950 lane swaps (v_permlane32_swap, v_permlane16_swap), then run a DPP
-// butterfly inside each row (quad_perm 1,0,3,2 / 2,3,0,1, row_half_mirror,
-// row_mirror); every lane then holds the result, read once with
-// v_readfirstlane.  The result is wave-uniform.
+// 32-bit reductions that go to a scalar register (max_i32, sum_i32, min_u32) fold by
+// DPP alone into lane 63, row shifts and then row broadcasts (fold_to_last).  Those
+// that leave the result in every lane (sum_i32_all, sum4_i32, min_u32_all) first fold
+// the four 16-lane rows onto each other with the gfx950 lane swaps
+// (v_permlane32_swap, v_permlane16_swap), then run a DPP butterfly inside each row
+// (quad_perm 1,0,3,2 / 2,3,0,1, row_half_mirror, row_mirror).
 #pragma once
 
 #include <hip/hip_runtime.h>
