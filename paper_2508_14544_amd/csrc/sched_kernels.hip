@@ -480,13 +480,35 @@ sk::Params result_params(const sched_instances_t* in, int64_t M, const sched_res
 }
 
 // Whether a batch of K instances of at most nmax requests runs a lane per
-// instance (k_tiny).  Instances of up to two requests always (12 us a call
-// against 26 to 40 with a wave each, A_min, at any K up to 4096); of up to eight
-// once a wave each would take more than five rounds of the 16 waves per CU (A_min,
-// 6 requests, lane against wave: 118 and 100 us at 16384 instances, 124 and 297 us
-// at 65536; 8 requests: 163 and 115, 179 and 360 us).
-bool tiny_batch(int64_t nmax, int64_t K, int n_cu) {
-  return nmax <= 2 || (nmax <= sk::kTinyRequests && K > 5 * 16 * static_cast<int64_t>(n_cu));
+// instance (k_tiny).  64 instances to a wave last as long as the longest of them, at any K
+// up to 262144, while a wave each takes a time that grows with the rounds of 16 waves a
+// CU.  Where the two meet depends on how differently long the instances of a wave are.
+// From about five rounds on a lane each is ahead or near, but for A_l and A_min of five
+// requests or more: promotions and cancellations differ from instance to instance, and A_min
+// may cancel hundreds of times where requests are long and the memory is short.  Their
+// lines lie between the mixes that suit lanes best and least.  Lane / wave in us,
+// (a) the competitive-ratio study's instances (outputs to 6, M = 12), (b) outputs to 512,
+// M = 1024, (c) outputs to 32, intervals 1 to 64, M = 96:
+//   1 or 2 requests: A_min 11 / 24 for one instance, 24 / 26 for 2048; A_l 33 / 26 for 512,
+//     38 / 33 for 8192, 35 / 47 for 16384
+//   3 or 4, 20481 instances: A_min 79 / 80, A_l 92 / 80, the others 0.4 to 0.7 of a wave
+//   5: A_l 118 / 93 at 20481, 119 / 103 at 24577; A_min (b) 357 / 186, (c) 77 / 89 at 24577
+//   6: A_l 150 / 117 at 24577, 149 / 151 at 32768; A_min (a) 139 / 128, (b) 723 / 320 at 24577,
+//     155 / 153, 772 / 381 at 32768
+//   8: A_l (a) 206 / 140, (c) 73 / 146 at 24577, (a) 212 / 184, (c) 73 / 190 at 32768; A_min (a) 204 /
+//     186, (b) 2277 / 989 at 32768, 210 / 259, 2341 / 1402 at 49153, 246 / 633, 2419 / 3310 at 131072;
+//     A_random (b) 122 / 79 at 20481, 118 / 90 at 24577, 119 / 158 at 49153; H-SF (a) 91 / 68 at
+//     20481, 93 / 97 at 32768; A_max 0.7 to 1.0 of a wave at 20481
+// The adaptive policy may run every instance as A_min.
+bool tiny_batch(int algo, int64_t nmax, int64_t K, int n_cu) {
+  if (nmax > sk::kTinyRequests) return false;
+  const bool aell = algo == SCHED_AELL;
+  int rounds = 5;
+  if (nmax <= 2) rounds = aell ? 3 : 0;
+  else if (aell || algo == SCHED_AMIN || algo == SCHED_ADAPTIVE)
+    rounds = nmax <= 4 ? 5 : nmax == 5 ? 6 : nmax == 6 || aell ? 8 : 12;
+  else if (algo == SCHED_ARANDOM && nmax == 8) rounds = 6;
+  return K > rounds * 16 * static_cast<int64_t>(n_cu);
 }
 
 const void* tiny_kernel(int algo) {
@@ -682,7 +704,7 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
   // tiny instances: one launch, a lane each, and no workspace (unless an option
   // asks for a tier of the other kernels)
   if (!ww && forced_rows == 0 && o.evicted_capacity == 0 && o.evicted_lds_limit == 0 &&
-      tiny_batch(nmax, in->num_instances, n_cu)) {
+      tiny_batch(algo, nmax, in->num_instances, n_cu)) {
     sk::Params P = result_params(in, M, out, o.step_cap);
     hipError_t err = hipSuccess;
     if (o.event_before) err = hipEventRecord(static_cast<hipEvent_t>(o.event_before), st);

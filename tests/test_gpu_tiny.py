@@ -1,6 +1,6 @@
 """GPU parity of the kernel that gives every tiny instance a lane (64 instances to
 a wave; batches of instances of at most two requests, and large ones of at most
-eight) with the CPU oracle, at its edges: instances of 0 to 8 requests in one
+eight, how large being a matter of the policy) with the CPU oracle, at its edges: instances of 0 to 8 requests in one
 wave, batches that do not fill a wave, invalid instances among valid ones,
 arrivals, tie keys, step caps, long runs, and the wave-per-instance kernels on the
 same batch (an option that only they read selects them)."""
@@ -18,8 +18,10 @@ pytestmark = pytest.mark.gpu
 POLICIES = [O.AMAX, O.AMIN, O.HSF, O.AELL, O.ADAPTIVE, O.ARANDOM]
 # an LDS limit far above what a small instance's cancelled set can reach
 WAVE = dict(evicted_lds_limit=4096)
-# more instances than five rounds of 16 waves on each of 256 CUs; no multiple of 64
-MANY = 5 * 16 * 256 + 37
+# more instances than twelve rounds of 16 waves on each of 256 CUs, from which on every
+# policy gives them a lane each, and the rounds from which some do; no multiples of 64
+MANY = 12 * 16 * 256 + 37
+LINES = {1: (3,), 2: (3,), 3: (5,), 4: (5,), 5: (5, 6), 6: (5, 8), 7: (5, 8, 12), 8: (5, 6, 8, 12)}
 
 
 @pytest.fixture(scope="module")
@@ -59,6 +61,24 @@ def test_sizes_and_partial_waves(B, algo, n_max):
         assert_parity(b, g, oracle_run(b, algo))
         w = gpu_run(B, b, algo, **WAVE)
         assert all(np.array_equal(g[f], w[f]) for f in g if g[f] is not None)
+
+
+@pytest.mark.parametrize("algo", POLICIES)
+@pytest.mark.parametrize("n_max", sorted(LINES))
+def test_both_sides_of_the_lines(B, algo, n_max):
+    few = W.random_small(n_max, 500, n_max, s_max=7, o_max=9, M=40, arrivals=True)
+    few = W.with_random_order(few, n_max)
+    ref = oracle_run(few, algo)
+    for rounds in LINES[n_max]:
+        for count in (rounds * 16 * 256, rounds * 16 * 256 + 1):
+            b = many_of(few, count)
+            assert b.max_requests == n_max
+            g = gpu_run(B, b, algo, no_alloc=count % 2 == 0)
+            at = np.arange(count) % few.num_instances
+            for f in ("status", "tel", "makespan", "request_steps", "total_evictions"):
+                assert np.array_equal(g[f], ref[f][at]), f
+            for f in ("completion", "evictions"):
+                assert np.array_equal(g[f], np.resize(ref[f], b.total_requests)), f
 
 
 @pytest.mark.parametrize("algo", POLICIES)
