@@ -50,8 +50,8 @@ extern template __global__ void k_simulate_group<SCHED_AMIN, 8, 16, true>(Params
 // one after the other for lack of LDS, the CU's next four waves may share SIMDs (3 to 10
 // in 100 of 1024 waves on 256 CUs did, none after this kernel).  A simulation lasts as
 // long as its slowest instance, and a wave that shares its SIMD is slower: 1024 x 10000
-// A_l took 26.9 ms instead of 22.9, A_min 27.0 instead of 24.1.  Needed where a CU gets
-// more than two waves (with two none met) and all are resident at once.
+// A_l took 26.9 ms instead of 22.9, A_min 27.0 instead of 24.1.  Where it is
+// launched: prepare_launch.
 __global__ __launch_bounds__(64) void k_spread() { __builtin_amdgcn_s_sleep(64); }
 
 // Issue-priority classes (A_min with upper bounds, from k_prepare): kept only
@@ -271,11 +271,16 @@ const void* prepare_kernel(int algo) {
 // a CU hold several workgroups of them, else sixteen.  Measured, with 1 / 4 / 16
 // waves an instance: 65536 x 2000 2.32 / 1.45 / 3.84 ms, 1024 x 10000 0.79 / 0.43 /
 // 0.27 ms, 3000 x 1500 with tie keys 173 / 87 / 325 us, 4096 x 1000 58 / 50 / 192 us.
+// k_spread takes 2 to 5 us of the call.  With it, against without, on 256 CUs: 1500 to 3000
+// requests 0.85 to 0.92 of the time at 1024 and 2048 instances, 0.89 to 0.96 at 3072, 0.98 to 1.01
+// at the counts between (a CU's last SIMDs then hold one wave fewer than the others
+// anyway) but 0.91 for 2816 of A_l; 300 to 1000 requests 1.00 to 1.03 up to 2560, 0.89 to 0.97 at
+// 3072, 0.93 to 1.03 at 2816.  Above 12 a CU some SIMD has four waves in any order: 1.00 to 1.02.
 PrepareLaunch prepare_launch(int algo, int64_t nmax, int64_t K, int n_cu, bool tie, int lds_max) {
   // A_l sorts nothing but tie keys
   const size_t lds = (tie ? 12 : algo == SCHED_AELL ? 4 : 8) * static_cast<size_t>(std::max<int64_t>(nmax, 1));
   if (nmax <= 64 || (nmax <= 256 && K > 2 * int64_t(n_cu))) return {prepare_kernel<1, true>(algo), 1, lds, false};
-  const bool spread = K > 2 * int64_t(n_cu) && K <= 16 * int64_t(n_cu);
+  const bool spread = K <= 12 * int64_t(n_cu) && K > (nmax > 1024 ? 2 : 8) * int64_t(n_cu);
   if (nmax <= 4096) return {prepare_kernel<4, true>(algo), 4, lds, spread};
   if (lds + sizeof(sk::PrepareShared<16>) <= static_cast<size_t>(lds_max))
     return {prepare_kernel<16, true>(algo), 16, lds, spread};
