@@ -24,25 +24,8 @@ extern template __global__ void k_simulate_ladder_wide<SCHED_HSF>(Params);
 extern template __global__ void k_simulate_ladder_wide<SCHED_AELL>(Params);
 extern template __global__ void k_simulate_ladder_wide<SCHED_ARANDOM>(Params);
 // defined in sched_group.hip
-extern template __global__ void k_simulate_group<SCHED_AMAX, 2, 8, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_AMAX, 4, 4, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_AMAX, 4, 16, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_AMAX, 8, 16, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_HSF, 2, 8, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_HSF, 4, 4, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_HSF, 4, 16, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_HSF, 8, 16, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_ARANDOM, 4, 16, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_ARANDOM, 8, 16, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_AELL, 4, 16, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_AELL, 8, 16, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_AMIN, 2, 8, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_AMIN, 2, 8, true>(Params);
-extern template __global__ void k_simulate_group<SCHED_AMIN, 4, 4, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_AMIN, 4, 4, true>(Params);
-extern template __global__ void k_simulate_group<SCHED_AMIN, 4, 16, false>(Params);
-extern template __global__ void k_simulate_group<SCHED_AMIN, 4, 16, true>(Params);
-extern template __global__ void k_simulate_group<SCHED_AMIN, 8, 16, true>(Params);
+SK_GROUP_KERNELS(extern)
+SK_GROUP_KERNELS_AMIN(extern)
 
 // One wave an instance that sleeps until all of them have started (about 2 us).  A
 // CU gives a new wave the SIMD that follows the last one's, as long as waves end in the
@@ -191,33 +174,41 @@ struct Tier {
   int list;         // a retry pass over a list of the instances that it takes (k_retry_list)
 };
 
-// The workgroup kernels that exist (sched_group.hip), else NULL.
+// The workgroup kernels that exist (sched_group.hip), else NULL.  list: over a list of
+// the instances (retry passes).
+template <int ALGO, int W, bool VGLOBAL>
+const void* group_retry_kernel(bool list) {
+  return list ? reinterpret_cast<const void*>(&sk::k_simulate_group<ALGO, W, 16, VGLOBAL, true>)
+              : reinterpret_cast<const void*>(&sk::k_simulate_group<ALGO, W, 16, VGLOBAL, false>);
+}
+
+template <int ALGO, bool VGLOBAL>
+const void* group_first_kernel(int w) {
+  return w == 2 ? reinterpret_cast<const void*>(&sk::k_simulate_group<ALGO, 2, 8, VGLOBAL, false>)
+                : reinterpret_cast<const void*>(&sk::k_simulate_group<ALGO, 4, 4, VGLOBAL, false>);
+}
+
 template <int ALGO>
-const void* group_kernel(int w, int rows, bool vglobal) {
-  using P = sk::Params;
-  void (*f)(P) = nullptr;
-  if constexpr (ALGO == SCHED_AMAX || ALGO == SCHED_HSF) {
-    if (!vglobal) {
-      if (w == 2 && rows == 8) f = &sk::k_simulate_group<ALGO, 2, 8, false>;
-      if (w == 4 && rows == 4) f = &sk::k_simulate_group<ALGO, 4, 4, false>;
-    }
-  }
-  if constexpr (ALGO != SCHED_AMIN) {
-    if (!vglobal && w == 4 && rows == 16) f = &sk::k_simulate_group<ALGO, 4, 16, false>;
-    if (!vglobal && w == 8 && rows == 16) f = &sk::k_simulate_group<ALGO, 8, 16, false>;
+const void* group_kernel(int w, int rows, bool vglobal, bool list) {
+  const bool first = (w == 2 && rows == 8) || (w == 4 && rows == 4);
+  if (!first && (rows != 16 || (w != 4 && w != 8))) return nullptr;
+  if (first && list) return nullptr;
+  if constexpr (ALGO == SCHED_AMIN) {
+    if (first) return vglobal ? group_first_kernel<ALGO, true>(w) : group_first_kernel<ALGO, false>(w);
+    if (w == 8) return vglobal ? group_retry_kernel<ALGO, 8, true>(list) : nullptr;
+    return vglobal ? group_retry_kernel<ALGO, 4, true>(list) : group_retry_kernel<ALGO, 4, false>(list);
   } else {
-    if (w == 2 && rows == 8) f = vglobal ? &sk::k_simulate_group<ALGO, 2, 8, true> : &sk::k_simulate_group<ALGO, 2, 8, false>;
-    if (w == 4 && rows == 4) f = vglobal ? &sk::k_simulate_group<ALGO, 4, 4, true> : &sk::k_simulate_group<ALGO, 4, 4, false>;
-    if (w == 4 && rows == 16)
-      f = vglobal ? &sk::k_simulate_group<ALGO, 4, 16, true> : &sk::k_simulate_group<ALGO, 4, 16, false>;
-    if (w == 8 && rows == 16 && vglobal) f = &sk::k_simulate_group<ALGO, 8, 16, true>;
+    if (vglobal) return nullptr;
+    if constexpr (ALGO == SCHED_AMAX || ALGO == SCHED_HSF)
+      if (first) return group_first_kernel<ALGO, false>(w);
+    if (first) return nullptr;
+    return w == 8 ? group_retry_kernel<ALGO, 8, false>(list) : group_retry_kernel<ALGO, 4, false>(list);
   }
-  return reinterpret_cast<const void*>(f);
 }
 
 template <int ALGO>
 const void* sim_kernel(const Tier& tr, bool ordered, bool classes, bool rounds) {
-  if (tr.gw > 1) return group_kernel<ALGO>(tr.gw, tr.rows, tr.vglobal);
+  if (tr.gw > 1) return group_kernel<ALGO>(tr.gw, tr.rows, tr.vglobal, tr.list != 0);
   if constexpr (ALGO == SCHED_AMIN) {
     if (tr.grow && !tr.wide && ordered)
       return reinterpret_cast<const void*>(&sk::k_simulate_ladder<ALGO, true, false, false>);
@@ -364,7 +355,7 @@ int build_tiers(int algo, int64_t nmax, int64_t K, int forced_rows, int cap0, in
     }
     const int64_t want = std::min<int64_t>(need_v, 16384);
     const int64_t fit = std::min<int64_t>(group_cap_fit(algo, w, rows, rm), cap_fit);
-    const bool lds = fit >= want && group_kernel<SCHED_AMIN>(w, rows, false) != nullptr;
+    const bool lds = fit >= want && group_kernel<SCHED_AMIN>(w, rows, false, false) != nullptr;
     if (lds) out[m++] = Tier{rows, false, false, mask != 0, false, static_cast<int>(want), mask, 0, 0, 0, w, 0};
     if (!lds || want < need_v) out[m++] = Tier{rows, false, false, true, true, 0, lds ? 2 : (mask ? mask : 0), 0, 0, 0, w, 0};
   };
@@ -661,7 +652,9 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
       // every 256th or one in 20 runs 1200 requests at once, H-SF: 4.1, 5.9 and 37 ms;
       // a workgroup an instance 7.2, 89 and 73 (the device gives workgroups to its XCDs
       // in turn), 4096 workgroups with fixed shares 44, 89 and 45.
-      if (t.gw > 1 && t.run_mask != 0 && in->num_instances > 16 * int64_t(n_cu)) {
+      // (After a first launch of workgroups, only A_min instances whose cancelled set is
+      // beyond 16384 entries are taken again: fixed shares.)
+      if (t.gw > 1 && t.rows == 16 && t.run_mask != 0 && in->num_instances > 16 * int64_t(n_cu)) {
         t.list = 1;
         t.grid = std::min(t.grid > 0 ? t.grid : INT32_MAX, 4 * n_cu);
       }

@@ -123,8 +123,8 @@ struct Params {
   int32_t* order;
   int32_t* okey;
   int32_t* obucket;
-  // retry passes of fewer workgroups than instances: the instances that the pass
-  // takes, their number, and a cursor over them (NULL: workgroup g takes g, g + grid, ...)
+  // retry passes over a list (k_simulate_group, LISTED): the instances that the pass
+  // takes, their number, and a cursor over them
   int32_t* retry_list;
   int32_t* retry_count;  // [0] the number, [1] the cursor
   int32_t retry_room;    // entries that the list holds
@@ -1254,15 +1254,17 @@ __device__ __forceinline__ void sim_instance(const Params& P, const int k, const
 // instances an earlier pass handed over run.
 // Workgroup g simulates instances g, g + grid, ... (a launch with global
 // cancelled sets has fewer workgroups than instances: each workgroup's sets
-// are its own), or with P.retry_list the next one of the list until none is left:
-// which instances of a batch need a retry pass may follow any pattern (a sweep has its
-// parameters in blocks), and each takes milliseconds.  A list too short for them (only
-// where offsets that decrease give the same requests to many instances) is not used.
-template <int ALGO, int W, int ROWS, bool VGLOBAL>
+// are its own).  LISTED (retry passes of large batches): it takes the next instance of
+// P.retry_list until none is left, since which instances of a batch need the pass may follow
+// any pattern (a sweep has its parameters in blocks), and each takes milliseconds; a list
+// too short for them (only where offsets that decrease give the same requests to many
+// instances) is not used.  A kernel of its own: with the list in the loop, the others
+// took up to 6% longer (one A_min instance of 100000 on 4 waves 419 ms, not 394).
+template <int ALGO, int W, int ROWS, bool VGLOBAL, bool LISTED = false>
 __global__ __launch_bounds__(64 * W) void k_simulate_group(Params P) {
   extern __shared__ uint64_t lds64[];
-  const bool listed = P.retry_list != nullptr && P.retry_count[0] <= P.retry_room;
-  for (int g = blockIdx.x;; g += gridDim.x) {
+  const bool listed = LISTED && P.retry_count[0] <= P.retry_room;
+  for (int g = blockIdx.x; listed || g < P.K; g += gridDim.x) {
     int k = g;
     if (listed) {
       if (threadIdx.x == 0) lds64[0] = static_cast<uint64_t>(atomicAdd(&P.retry_count[1], 1));
@@ -1272,7 +1274,6 @@ __global__ __launch_bounds__(64 * W) void k_simulate_group(Params P) {
       if (k >= P.retry_count[0]) return;
       k = P.retry_list[k];
     }
-    if (k >= P.K) return;
     if (!listed && P.algo_of && P.algo_of[k] != ALGO) continue;
     int st0 = P.status[k];
     if (P.run_mask) {
@@ -1283,6 +1284,33 @@ __global__ __launch_bounds__(64 * W) void k_simulate_group(Params P) {
     __syncthreads();  // the next instance reuses the LDS
   }
 }
+
+// The workgroup kernels of a policy: EACH(...) instantiates them, with `extern` before
+// it they are declared to the host code that launches them.  2 x 8 and 4 x 4 waves and rows
+// (1024 runs) as a first launch, 4 x 16 and 8 x 16 (4096 and 8192 runs) as retry passes.
+#define SK_GROUP_FIRST(EACH, ALGO, VGLOBAL)                                                \
+  EACH template __global__ void k_simulate_group<ALGO, 2, 8, VGLOBAL, false>(Params);      \
+  EACH template __global__ void k_simulate_group<ALGO, 4, 4, VGLOBAL, false>(Params);
+#define SK_GROUP_RETRY(EACH, ALGO, W, VGLOBAL)                                             \
+  EACH template __global__ void k_simulate_group<ALGO, W, 16, VGLOBAL, false>(Params);     \
+  EACH template __global__ void k_simulate_group<ALGO, W, 16, VGLOBAL, true>(Params);
+#define SK_GROUP_KERNELS(EACH)                                                             \
+  SK_GROUP_FIRST(EACH, SCHED_AMAX, false)                                                  \
+  SK_GROUP_RETRY(EACH, SCHED_AMAX, 4, false)                                               \
+  SK_GROUP_RETRY(EACH, SCHED_AMAX, 8, false)                                               \
+  SK_GROUP_FIRST(EACH, SCHED_HSF, false)                                                   \
+  SK_GROUP_RETRY(EACH, SCHED_HSF, 4, false)                                                \
+  SK_GROUP_RETRY(EACH, SCHED_HSF, 8, false)                                                \
+  SK_GROUP_RETRY(EACH, SCHED_ARANDOM, 4, false)                                            \
+  SK_GROUP_RETRY(EACH, SCHED_ARANDOM, 8, false)                                            \
+  SK_GROUP_RETRY(EACH, SCHED_AELL, 4, false)                                               \
+  SK_GROUP_RETRY(EACH, SCHED_AELL, 8, false)
+#define SK_GROUP_KERNELS_AMIN(EACH)                                                        \
+  SK_GROUP_FIRST(EACH, SCHED_AMIN, false)                                                  \
+  SK_GROUP_FIRST(EACH, SCHED_AMIN, true)                                                   \
+  SK_GROUP_RETRY(EACH, SCHED_AMIN, 4, false)                                               \
+  SK_GROUP_RETRY(EACH, SCHED_AMIN, 4, true)                                                \
+  SK_GROUP_RETRY(EACH, SCHED_AMIN, 8, true)
 #undef SK_SET_PRIORITY
 #undef SK_LOAD_ARRIVALS
 #undef SK_PICK
