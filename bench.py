@@ -42,6 +42,7 @@ def kernel_source_hash() -> str:
     # the kernel sources and the build script (its compiler flags shape the code)
     for p in ("paper_2508_14544_amd/csrc/sched_kernels.hip", "paper_2508_14544_amd/csrc/sim_device.hpp",
               "paper_2508_14544_amd/csrc/sched_wide.hip", "paper_2508_14544_amd/csrc/sched_group.hip",
+              "paper_2508_14544_amd/csrc/sched_group_amin.hip",
               "paper_2508_14544_amd/csrc/wave.hpp",
               "paper_2508_14544_amd/csrc/sim_wave.hpp", "paper_2508_14544_amd/csrc/sim_tiny.hpp", "paper_2508_14544_amd/csrc/prepare.hpp",
               "paper_2508_14544_amd/csrc/sched_wave_amax.hip",

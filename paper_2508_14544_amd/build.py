@@ -10,7 +10,8 @@ ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libschedsim.so")
 SOURCES = [os.path.join(PKG, "csrc", f) for f in
            ("sched_wave_amin.hip", "sched_wave_aell.hip", "sched_wave_amax.hip", "sched_wave_hsf.hip",
-            "sched_wave_arandom.hip", "sched_wide.hip", "sched_group.hip", "sched_kernels.hip", "opt_kernels.hip")]
+            "sched_wave_arandom.hip", "sched_wide.hip", "sched_group.hip", "sched_group_amin.hip", "sched_kernels.hip",
+            "opt_kernels.hip")]
 HEADERS = [os.path.join(PKG, "csrc", "wave.hpp"), os.path.join(PKG, "csrc", "sim_device.hpp"),
            os.path.join(PKG, "csrc", "sim_wave.hpp"), os.path.join(PKG, "csrc", "sim_tiny.hpp"),
            os.path.join(PKG, "csrc", "prepare.hpp"),
@@ -35,11 +36,15 @@ SPLIT_FLAGS = ["-DSK_SEPARATE_KERNELS"]
 # leaves uniform regions alone) and the flags that scope exits would set for the
 # lifetime markers, such a branch is one scalar compare and jump.  Together with
 # code written for it, 1.2 times faster over all policies.
-SIM_FLAGS = ["-mllvm", "--amdgpu-sched-strategy=iterative-ilp", "-mllvm", "-structurizecfg-skip-uniform-regions",
-             "-Xclang", "-disable-lifetime-markers"]
+SIM_FLAGS = ["-mllvm", "--amdgpu-sched-strategy=iterative-ilp", "-mllvm", "-structurizecfg-skip-uniform-regions"]
+NO_MARKERS = ["-Xclang", "-disable-lifetime-markers"]
+# The workgroup kernels other than A_min's keep the markers: without them one instance of
+# 100000 on 4 waves took 272 ms instead of 250 (A_max) and 157 instead of 135 (H-SF), where
+# A_min took 397 instead of 428.
+KEEP_MARKERS = ("sched_group.hip",)
 
 
-def _compile(sources, lib, verbose, extra):
+def _compile(sources, lib, verbose, extra, flags_of=lambda name: ()):
     """Each translation unit to an object (concurrently, in _build/), then one
     shared library (every object carries its own device code)."""
     objdir = os.path.join(ROOT, "_build")
@@ -48,7 +53,7 @@ def _compile(sources, lib, verbose, extra):
     objs, procs = [], []
     for src in sources:
         obj = os.path.join(objdir, os.path.basename(src) + f".{tag}.o")
-        cmd = [HIPCC, *[f for f in FLAGS if f != "-shared"], *extra, "-c", src, "-o", obj]
+        cmd = [HIPCC, *[f for f in FLAGS if f != "-shared"], *flags_of(os.path.basename(src)), *extra, "-c", src, "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((subprocess.Popen(cmd), cmd))
@@ -68,7 +73,8 @@ def _compile(sources, lib, verbose, extra):
 
 def build(verbose: bool = True, extra=()) -> str:
     """Compile libschedsim.so and libschedprobe.so (always recompiles)."""
-    _compile(SOURCES, LIB, verbose, [*SIM_FLAGS, *SPLIT_FLAGS, *extra])
+    _compile(SOURCES, LIB, verbose, [*SIM_FLAGS, *SPLIT_FLAGS, *extra],
+             lambda name: () if name in KEEP_MARKERS else NO_MARKERS)
     _compile(PROBE_SOURCES, PROBE_LIB, verbose, extra)
     return LIB
 

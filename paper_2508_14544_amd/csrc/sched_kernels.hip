@@ -1,7 +1,7 @@
 // sched_kernels.hip -- the C ABI of the scheduler simulator (host side), the
 // preparation and launch-order kernels and, unless SK_SEPARATE_KERNELS leaves
 // them to sched_wave_*.hip (built concurrently), the one-wave kernels.  The wide
-// row ladder (sched_wide.hip) and the workgroup kernels (sched_group.hip) are
+// row ladder (sched_wide.hip) and the workgroup kernels (sched_group*.hip) are
 // translation units of their own.  The device code is in sim_wave.hpp and
 // sim_device.hpp.
 #include "prepare.hpp"
@@ -174,7 +174,7 @@ struct Tier {
   int list;         // a retry pass over a list of the instances that it takes (k_retry_list)
 };
 
-// The workgroup kernels that exist (sched_group.hip), else NULL.  list: over a list of
+// The workgroup kernels that exist (sched_group*.hip), else NULL.  list: over a list of
 // the instances (retry passes).
 template <int ALGO, int W, bool VGLOBAL>
 const void* group_retry_kernel(bool list) {
