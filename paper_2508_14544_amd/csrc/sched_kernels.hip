@@ -649,9 +649,9 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
       // workgroup started for each of them costs 200 us at 65536.  A grid that the
       // device holds at once (two or three workgroups a CU) goes through a list of
       // them instead, also where many need it: 65536 instances of which every 4096th,
-      // every 256th or one in 20 runs 1200 requests at once, H-SF: 4.1, 5.9 and 37 ms;
-      // a workgroup an instance 7.2, 89 and 73 (the device gives workgroups to its XCDs
-      // in turn), 4096 workgroups with fixed shares 44, 89 and 45.
+      // every 256th or one in 20 runs 1200 requests at once, H-SF: 3.2, 5.5 and 17 ms;
+      // a workgroup an instance 4.9, 37 and 62 (the device gives workgroups to its XCDs
+      // in turn), 4096 workgroups with fixed shares 44, 88 and 148.
       // (After a first launch of workgroups, only A_min instances whose cancelled set is
       // beyond 16384 entries are taken again: fixed shares.)
       if (t.gw > 1 && t.rows == 16 && t.run_mask != 0 && in->num_instances > 16 * int64_t(n_cu)) {
