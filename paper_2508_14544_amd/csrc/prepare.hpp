@@ -255,9 +255,10 @@ __global__ __launch_bounds__(64) void k_validate(Params P) {
 }
 
 // LDS: the sort buffers of max_requests entries are in LDS (with tie keys a third
-// one holds these), else in the workspace.
+// one holds these), else in the workspace.  retry_count: the retry passes' counts, to be
+// cleared (or NULL).
 template <int ALGO, int W, bool LDS>
-__global__ __launch_bounds__(64 * W) void k_prepare(Params P) {
+__global__ __launch_bounds__(64 * W) void k_prepare(Params P, int32_t* retry_count) {
   __shared__ PrepareShared<W> sh;
   extern __shared__ uint32_t pre_buf[];
   constexpr int kStride = 64 * W;
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(64 * W) void k_prepare(Params P) {
   const bool tie = P.tie_key != nullptr;
   uint32_t* const ka = LDS ? pre_buf : P.sort_a + b;
   uint32_t* const kb = LDS ? pre_buf + P.max_requests : P.sort_b + b;
-  if (P.retry_count && k == 0 && tid < kRetryCounts) P.retry_count[tid] = 0;
+  if (retry_count && k == 0 && tid < kRetryCounts) retry_count[tid] = 0;
 
   // ---- checks; per-request outputs start as "not completed, never cancelled"
   // (with tie keys, the staging arrays the kernels write too); without tie keys,

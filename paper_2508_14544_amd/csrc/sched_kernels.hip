@@ -65,17 +65,17 @@ __global__ __launch_bounds__(256) void k_prio_classes(Params P) {
 // The instances that a retry pass takes, in no particular order (algo: the policy
 // of the pass, in adaptive runs).  All are counted, those that the list has room for
 // are listed.
-__global__ __launch_bounds__(256) void k_retry_list(Params P, int algo) {
+__global__ __launch_bounds__(256) void k_retry_list(Params P, RetryList R, int algo) {
   const int k = blockIdx.x * 256 + static_cast<int>(threadIdx.x);
   const int lane = static_cast<int>(threadIdx.x & 63u);
   const bool take = k < P.K && !(P.algo_of && P.algo_of[k] != algo) && retry_takes(P, P.status[k]);
   const uint64_t m = __builtin_amdgcn_ballot_w64(take);
   if (m == 0) return;
   int base = 0;
-  if (lane == 0) base = atomicAdd(&P.retry_count[0], __builtin_popcountll(m));
+  if (lane == 0) base = atomicAdd(&R.count[0], __builtin_popcountll(m));
   base = __builtin_amdgcn_readfirstlane(base);
   const int at = base + __builtin_popcountll(m & ((1ull << lane) - 1ull));
-  if (take && at < P.retry_room) P.retry_list[at] = k;
+  if (take && at < R.room) R.list[at] = k;
 }
 
 // Launch order (A_min batches served in several rounds of waves): the
@@ -178,14 +178,14 @@ struct Tier {
 // the instances (retry passes).
 template <int ALGO, int W, bool VGLOBAL>
 const void* group_retry_kernel(bool list) {
-  return list ? reinterpret_cast<const void*>(&sk::k_simulate_group<ALGO, W, 16, VGLOBAL, true>)
-              : reinterpret_cast<const void*>(&sk::k_simulate_group<ALGO, W, 16, VGLOBAL, false>);
+  return list ? reinterpret_cast<const void*>(&sk::k_simulate_group_listed<ALGO, W, VGLOBAL>)
+              : reinterpret_cast<const void*>(&sk::k_simulate_group<ALGO, W, 16, VGLOBAL>);
 }
 
 template <int ALGO, bool VGLOBAL>
 const void* group_first_kernel(int w) {
-  return w == 2 ? reinterpret_cast<const void*>(&sk::k_simulate_group<ALGO, 2, 8, VGLOBAL, false>)
-                : reinterpret_cast<const void*>(&sk::k_simulate_group<ALGO, 4, 4, VGLOBAL, false>);
+  return w == 2 ? reinterpret_cast<const void*>(&sk::k_simulate_group<ALGO, 2, 8, VGLOBAL>)
+                : reinterpret_cast<const void*>(&sk::k_simulate_group<ALGO, 4, 4, VGLOBAL>);
 }
 
 template <int ALGO>
@@ -743,9 +743,10 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
   P.order = ord && ladder ? reinterpret_cast<int32_t*>(base + o_or) : nullptr;
   P.okey = P.order ? P.order + K : nullptr;
   P.obucket = P.order ? P.okey + K : nullptr;
+  int32_t* retry_count = nullptr;
   for (int a = 0; a < n_sim; ++a)
     for (int p = 0; p < n_tiers[a]; ++p)
-      if (tiers[a][p].list) P.retry_count = reinterpret_cast<int32_t*>(base + off);
+      if (tiers[a][p].list) retry_count = reinterpret_cast<int32_t*>(base + off);
   P.nw_max = nw;
   P.nw1_max = nw1;
   P.run_cap = forced_rows > 0 ? forced_rows * 64 : INT32_MAX;
@@ -758,7 +759,7 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
     // itself declares, at most PrepareShared<16>)
     if (pl.lds + sizeof(sk::PrepareShared<16>) > 65536)
       err = hipFuncSetAttribute(pl.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(pl.lds));
-    void* args[] = {&P};
+    void* args[] = {&P, &retry_count};
     if (err == hipSuccess) err = hipLaunchKernel(pl.kernel, dim3(P.K), dim3(64 * pl.waves), args, pl.lds, st);
     if (pl.spread) hipLaunchKernelGGL(sk::k_spread, dim3(P.K), dim3(64), 0, st);
   }
@@ -815,17 +816,18 @@ int simulate_impl(const sched_instances_t* in, int32_t algo, int64_t M, const sc
       q.retry_v_status = t.v_status;
       q.run_mask = t.run_mask;
       q.stage_comp = t.stage;
+      sk::RetryList rl{};
       if (t.list) {
         // (the sort buffer is free now and has room for them: every listed instance has
         // more than 640 requests, of its own unless offsets decrease; the adaptive
         // policy's two passes run at the same time)
-        q.retry_list = reinterpret_cast<int32_t*>(P.sort_a) + (a == 1 ? N / 2 : 0);
-        q.retry_room = static_cast<int32_t>(std::min<size_t>(n_sim == 2 ? N / 2 : N, INT32_MAX));
-        q.retry_count = P.retry_count + 2 * (8 * a + p);
-        hipLaunchKernelGGL(sk::k_retry_list, dim3((P.K + 255) / 256), dim3(256), 0, sa, q, sim_algos[a]);
+        rl.list = reinterpret_cast<int32_t*>(P.sort_a) + (a == 1 ? N / 2 : 0);
+        rl.room = static_cast<int32_t>(std::min<size_t>(n_sim == 2 ? N / 2 : N, INT32_MAX));
+        rl.count = retry_count + 2 * (8 * a + p);
+        hipLaunchKernelGGL(sk::k_retry_list, dim3((P.K + 255) / 256), dim3(256), 0, sa, q, rl, sim_algos[a]);
         err = hipGetLastError();
       }
-      void* args[] = {&q};
+      void* args[] = {&q, &rl};  // (the list: its kernels alone)
       const dim3 tgrid(t.grid > 0 ? t.grid : P.K), tblock(64 * (t.gw > 1 ? t.gw : 1));
       // (a launch over every instance may take them in the launch order)
       if (err == hipSuccess)

@@ -123,11 +123,14 @@ struct Params {
   int32_t* order;
   int32_t* okey;
   int32_t* obucket;
-  // retry passes over a list (k_simulate_group, LISTED): the instances that the pass
-  // takes, their number, and a cursor over them
-  int32_t* retry_list;
-  int32_t* retry_count;  // [0] the number, [1] the cursor
-  int32_t retry_room;    // entries that the list holds
+};
+
+// Retry passes over a list (k_simulate_group_listed): the instances that the pass
+// takes, their number, and a cursor over them.
+struct RetryList {
+  int32_t* list;
+  int32_t* count;  // [0] the number, [1] the cursor
+  int32_t room;    // entries that the list holds
 };
 
 // Whether some request of the instance of n > 0 requests from b on arrives after
@@ -1254,33 +1257,44 @@ __device__ __forceinline__ void sim_instance(const Params& P, const int k, const
 // instances an earlier pass handed over run.
 // Workgroup g simulates instances g, g + grid, ... (a launch with global
 // cancelled sets has fewer workgroups than instances: each workgroup's sets
-// are its own).  LISTED (retry passes of large batches): it takes the next instance of
-// P.retry_list until none is left, since which instances of a batch need the pass may follow
-// any pattern (a sweep has its parameters in blocks), and each takes milliseconds; a list
-// too short for them (only where offsets that decrease give the same requests to many
-// instances) is not used.  A kernel of its own: with the list in the loop, the others
-// took up to 6% longer (one A_min instance of 100000 on 4 waves 419 ms, not 394).
-template <int ALGO, int W, int ROWS, bool VGLOBAL, bool LISTED = false>
+// are its own).
+template <int ALGO, int W, int ROWS, bool VGLOBAL>
 __global__ __launch_bounds__(64 * W) void k_simulate_group(Params P) {
-  extern __shared__ uint64_t lds64[];
-  const bool listed = LISTED && P.retry_count[0] <= P.retry_room;
-  for (int g = blockIdx.x; listed || g < P.K; g += gridDim.x) {
-    int k = g;
-    if (listed) {
-      if (threadIdx.x == 0) lds64[0] = static_cast<uint64_t>(atomicAdd(&P.retry_count[1], 1));
-      __syncthreads();
-      k = wave::uniform(static_cast<int32_t>(lds64[0]));
-      __syncthreads();  // the instance uses the LDS
-      if (k >= P.retry_count[0]) return;
-      k = P.retry_list[k];
-    }
-    if (!listed && P.algo_of && P.algo_of[k] != ALGO) continue;
+  for (int k = blockIdx.x; k < P.K; k += gridDim.x) {
+    if (P.algo_of && P.algo_of[k] != ALGO) continue;
     int st0 = P.status[k];
     if (P.run_mask) {
-      if (!listed && !retry_takes(P, st0)) continue;
+      if (!retry_takes(P, st0)) continue;
       st0 = SCHED_OK;
     }
     sim_instance<ALGO, ROWS, VGLOBAL, W>(P, k, st0, P.retry_status);
+    __syncthreads();  // the next instance reuses the LDS
+  }
+}
+
+// A retry pass of a large batch: a workgroup takes the next instance of R.list until none
+// is left, since which instances of a batch need the pass may follow any pattern (a sweep
+// has its parameters in blocks), and each takes milliseconds.  A list too short for them
+// (only where offsets that decrease give the same requests to many instances) is not used.
+// A kernel of its own: with the list in the other's loop, that took up to 6% longer (one
+// A_min instance of 100000 on 4 waves 419 ms, not 394).
+template <int ALGO, int W, bool VGLOBAL>
+__global__ __launch_bounds__(64 * W) void k_simulate_group_listed(Params P, RetryList R) {
+  extern __shared__ uint64_t lds64[];
+  const bool listed = R.count[0] <= R.room;
+  for (int g = blockIdx.x; listed || g < P.K; g += gridDim.x) {
+    int k = g;
+    if (listed) {
+      if (threadIdx.x == 0) lds64[0] = static_cast<uint64_t>(atomicAdd(&R.count[1], 1));
+      __syncthreads();
+      k = wave::uniform(static_cast<int32_t>(lds64[0]));
+      __syncthreads();  // the instance uses the LDS
+      if (k >= R.count[0]) return;
+      k = R.list[k];
+    } else if ((P.algo_of && P.algo_of[k] != ALGO) || !retry_takes(P, P.status[k])) {
+      continue;
+    }
+    sim_instance<ALGO, 16, VGLOBAL, W>(P, k, SCHED_OK, P.retry_status);
     __syncthreads();  // the next instance reuses the LDS
   }
 }
@@ -1289,11 +1303,11 @@ __global__ __launch_bounds__(64 * W) void k_simulate_group(Params P) {
 // it they are declared to the host code that launches them.  2 x 8 and 4 x 4 waves and rows
 // (1024 runs) as a first launch, 4 x 16 and 8 x 16 (4096 and 8192 runs) as retry passes.
 #define SK_GROUP_FIRST(EACH, ALGO, VGLOBAL)                                                \
-  EACH template __global__ void k_simulate_group<ALGO, 2, 8, VGLOBAL, false>(Params);      \
-  EACH template __global__ void k_simulate_group<ALGO, 4, 4, VGLOBAL, false>(Params);
+  EACH template __global__ void k_simulate_group<ALGO, 2, 8, VGLOBAL>(Params);             \
+  EACH template __global__ void k_simulate_group<ALGO, 4, 4, VGLOBAL>(Params);
 #define SK_GROUP_RETRY(EACH, ALGO, W, VGLOBAL)                                             \
-  EACH template __global__ void k_simulate_group<ALGO, W, 16, VGLOBAL, false>(Params);     \
-  EACH template __global__ void k_simulate_group<ALGO, W, 16, VGLOBAL, true>(Params);
+  EACH template __global__ void k_simulate_group<ALGO, W, 16, VGLOBAL>(Params);            \
+  EACH template __global__ void k_simulate_group_listed<ALGO, W, VGLOBAL>(Params, RetryList);
 #define SK_GROUP_KERNELS(EACH)                                                             \
   SK_GROUP_FIRST(EACH, SCHED_AMAX, false)                                                  \
   SK_GROUP_RETRY(EACH, SCHED_AMAX, 4, false)                                               \

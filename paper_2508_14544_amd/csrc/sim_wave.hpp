@@ -1279,7 +1279,8 @@ __global__ __launch_bounds__(64) void k_simulate(Params P) {
   if (P.algo_of && P.algo_of[k] != ALGO) return;  // adaptive run: the other policy's instance
   int st0 = P.status[k];
   if (RETRY_PASS) {
-    if (!retry_takes(P, st0)) return;
+    const bool take = (st0 == kRetryRows && (P.run_mask & 1)) || (st0 == kRetryV && (P.run_mask & 2));
+    if (!take) return;
     st0 = SCHED_OK;
   }
   WaveState st;
@@ -1300,7 +1301,8 @@ __device__ __forceinline__ void wide_ladder_instance(const Params& P, const int 
   int st0 = P.status[k];
   if (P.run_mask) {
     // a retry pass: only the instances an earlier pass handed over
-    if (!retry_takes(P, st0)) return;
+    const bool take = (st0 == kRetryRows && (P.run_mask & 1)) || (st0 == kRetryV && (P.run_mask & 2));
+    if (!take) return;
     st0 = SCHED_OK;
   }
   int arr_ptr = 0;
